@@ -16,23 +16,35 @@
 //      this sweep's shift.  No two workgroups write the same word, so the
 //      store needs no atomics and the shift keeps one-site granularity.
 //
-// LDS byte of a site holds the complemented slope bits: bit 0 = nx
-// (sigma_x = -1), bit 1 = ny (sigma_y = -1), bit 2 = block border (dead)
-// marker, bit 3 = copy of nx, bit 4 = copy of ny.  For the site s, its left
-// neighbour l and lower neighbour d, the five-bit code
-//   k = (s & 7) | (l & 8) | (d & 16)
-// holds nx(u,v), ny(u,v), dead(u,v), nx(u-1,v), ny(u,v-1).  k = 24 is a local
-// minimum (-1 +1; -1 +1), k = 3 a local maximum; a dead site never matches.
-// A minimum is thus s = 0 with l & 8 and d & 16 set, a test of two bit
-// operations.  An accepted move rewrites the three bytes (s ^ 0x1B, l ^ 0x09,
-// d ^ 0x12).
+// LDS byte of a site holds the complemented slope bits: bit 3 = nx
+// (sigma_x = -1), bit 7 = ny (sigma_y = -1), bit 0 = block border (dead) marker.
+// For the site s, its left neighbour l and lower neighbour d, a local minimum
+// (-1 +1; -1 +1) has s = 0, nx in l and ny in d; a local maximum has s = 0x88
+// and neither; a dead site is never 0 or 0x88.  Only lanes whose s is one of the
+// two read l and d, and one multiplexer and one comparison then decide.  An
+// accepted move rewrites the three bytes (s ^ 0x88, l ^ 0x08, d ^ 0x80).
 // Within a step no other lane reads or writes those bytes (sites attempted
 // together are never nearest or diagonal neighbours: each 8x8 cell has a dead
-// row and column), so plain byte stores suffice.
+// row and column), so plain byte stores suffice.  The two bits sit four apart so
+// that the expansion is one multiplication by 1 + 2^9 + 2^18 + 2^27 per four
+// sites and the packing one byte dot product.
 //
 // The height of site (0,0) is tracked without touching the attempt loop: the
-// block containing it compares the sigma_x count of its row prefix before and
-// after the steps (the row's block-border site never moves).
+// threads staging the row of the block that contains it count the sigma_x bonds
+// of the row's prefix in the packed words, before the steps and after them (the
+// row's block-border site never moves).  (One thread counting the row's bytes in
+// LDS took up to 7 us of the 22 us a sweep of one 256 x 256 block needed.)
+//
+// What bounds it: LDS.  Per attempt of 64 cells one full byte read (4.6 cycles of
+// the CU's LDS, half of it two cell rows meeting in the same banks), two reads of
+// the candidates (2 x 3.2) and three byte stores (4.45 each whatever the number
+// of lanes: address and data of a wave take four cycles to reach the LDS) are
+// 24.4 cycles, the staging about one, of the 27.8 measured at p = 1, q = 0 on
+// 32768^2 (777 us per sweep; 797 us with five bits per byte, two dependent tests
+// per attempt and 28 instead of 15 VALU cycles per four staged sites).  With
+// acceptance draws it is VALU issue: 254 us per sweep of 16384^2 at p = 0.95,
+// q = 0.05 (324 us when every fourth step computed its draws before its site
+// address instead of in the waits of the four steps before).
 #pragma once
 
 #include "okpz_internal.h"
@@ -109,26 +121,50 @@ __device__ __forceinline__ void philox_rounds(Ctr4 &c, uint32_t k0, uint32_t k1)
     }
 }
 
-// 4 bits -> 4 bytes (bit j to bit 0 of byte j): nib * (1 + 2^7 + 2^14 + 2^21)
-// puts bit j at positions j + 7i, all distinct (no carries); byte j keeps
-// i = j.
-__device__ __forceinline__ uint32_t spread4(uint32_t nib)
+// LDS byte of a site (complemented slope bits).
+constexpr uint32_t kNx = 0x08u, kNy = 0x80u, kDead = 0x01u;
+constexpr uint32_t kTop = kNx | kNy;  // a local maximum's byte; a minimum's is 0
+
+// 32 sites of a row, bits to bytes.  x and y hold the nx and ny bits reversed
+// (site u in bit 31 - u).  Word m of d gets sites 4m .. 4m+3.  A byte n with
+// the sites' nx in its low and ny in its high half times 1 + 2^9 + 2^18 + 2^27
+// puts bit 3 - i of n at bit 3 and bit 7 - i at bit 7 of byte i, and no two
+// copies of n overlap (they are 9 bits apart), so one mask leaves the bytes.
+__device__ __forceinline__ void expand32(uint32_t x, uint32_t y, uint32_t d[8])
 {
-    return __umul24(nib, 0x204081u) & 0x01010101u;
+    const uint32_t lo = __builtin_amdgcn_bitop3_b32(x, y << 4, 0x0F0F0F0Fu, 0xE4);
+    const uint32_t hi = __builtin_amdgcn_bitop3_b32(x >> 4, y, 0x0F0F0F0Fu, 0xE4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t a = lo >> (8 * k), b = hi >> (8 * k);
+        d[7 - 2 * k] = (__umul24(a & 0xffu, 0x40201u) + (a << 27)) & 0x88888888u;
+        d[6 - 2 * k] = (__umul24(b & 0xffu, 0x40201u) + (b << 27)) & 0x88888888u;
+    }
 }
 
-// 4 bytes with values in bit 0 -> 4 bits, scaled by `w` (byte weights)
-__device__ __forceinline__ uint32_t gather4(uint32_t bytes01, uint32_t w, uint32_t acc)
+// The inverse: the nx and ny bits (site u in bit u) of 32 site bytes.  The
+// weighted byte sum of four sites, 8 * (nx bits) + 128 * (ny bits), holds
+// their nx in bits 3..6 and their ny in bits 7..10.
+__device__ __forceinline__ void pack32(const uint32_t d[8], uint32_t &x, uint32_t &y)
 {
-    return __builtin_amdgcn_udot4(bytes01, w, acc, false);
-}
-
-// number of sigma_x = +1 bonds among the first n sites of a tile row
-__device__ __forceinline__ int row_prefix_bx(const uint8_t *row, int n)
-{
-    int c = 0;
-    for (int u = 0; u < n; ++u) c += (row[u] & 1) ^ 1;
-    return c;
+    uint32_t q[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t p[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            p[k] = __builtin_amdgcn_udot4(d[4 * h + k] & 0x88888888u, 0x08040201u, 0u, false);
+        // four bytes, each ny << 4 | nx of four sites
+        q[h] = (((p[1] << 8) | p[0]) >> 3) | (((p[3] << 8) | p[2]) << 13);
+    }
+    // nibbles of q[0] (sites 0..15) and q[1]: even ones are nx, odd ones ny
+    auto even = [](uint32_t v) {  // nibbles 0, 2, 4, 6 to the low half
+        v &= 0x0F0F0F0Fu;
+        v |= v >> 4;
+        return __builtin_amdgcn_perm(v, v, 0x0C0C0200u);
+    };
+    x = even(q[0]) | (even(q[1]) << 16);
+    y = even(q[0] >> 4) | (even(q[1] >> 4) << 16);
 }
 
 __device__ __forceinline__ int ilog2(uint32_t v) { return 31 - __builtin_clz(v); }
@@ -143,30 +179,17 @@ __host__ __device__ inline int group_size(int Bx, int By, int nblk)
     return g < 1 ? 1 : g;
 }
 
-// Eq. (1) on the five-bit code of a site byte s, its left neighbour's byte l
-// and its lower neighbour's byte d; r is the attempt's acceptance draw
-// (kDraw only).
+// Eq. (1) for a candidate site (byte s = 0, a possible minimum, or kTop, a
+// possible maximum) with its left and lower neighbours' bytes l and d: a
+// minimum needs nx in l and ny in d, a maximum neither.  The multiplexer (truth
+// table 0xE4: c ? a : b) takes bit 3 from l and the others from d; below bit 3
+// only the dead marker can be set.
 template <int kMode>
-__device__ __forceinline__ bool move_accepted(uint32_t sv, uint32_t lv, uint32_t dv,
-                                              uint32_t fixed_tbl, uint32_t r, uint64_t Tp,
-                                              uint64_t Tq)
+__device__ __forceinline__ bool move_allowed(uint32_t s, uint32_t l, uint32_t d)
 {
-    if (kMode == kGrowth) {
-        // minimum: s == 0 (nx = ny = 0 and copies, not dead), l & 8 (nx of
-        // the left bond) and d & 16 (ny of the lower bond) set:
-        // (~l & 8) | (~d & 16) | s == 0, two bit operations (truth table
-        // 0xAE: (~A & B) | C)
-        const uint32_t t = __builtin_amdgcn_bitop3_b32(lv, 8u, sv, 0xAE);
-        return __builtin_amdgcn_bitop3_b32(dv, 16u, t, 0xAE) == 0u;
-    }
-    // bitwise mux c ? a : b (truth table 0xE4): bit 3 from l, bit 4 from d,
-    // the others from s
-    const uint32_t t = __builtin_amdgcn_bitop3_b32(lv, dv, 8u, 0xE4);
-    const uint32_t code = __builtin_amdgcn_bitop3_b32(t, sv, 24u, 0xE4);
-    uint32_t tbl = fixed_tbl;
-    if (kMode == kDraw)
-        tbl = ((uint64_t)r < Tp ? (1u << 24) : 0u) | ((uint64_t)r < Tq ? (1u << 3) : 0u);
-    return (tbl >> code) & 1u;
+    uint32_t t = __builtin_amdgcn_bitop3_b32(l, d, kNx, 0xE4);
+    if (kMode != kGrowth) t ^= s;
+    return t >= kTop;
 }
 
 // Set the bits of *w selected by mask to those of v and keep the others; the
@@ -183,28 +206,9 @@ __device__ __forceinline__ void xor_byte(uint8_t *smem, uint32_t off, uint32_t v
     atomicXor(w, v << (8 * (off & 3u)));
 }
 
-// Origin of the cell grid in step 2m + odd of a block, from the block's
-// origin word m (x in byte 2 odd, y in byte 2 odd + 1): x << 16 and y << 16,
-// or (y << 16) | x.  A wave-uniform word (kUni) is unpacked with scalar
-// shifts; a per-lane word with one byte permute each.
-template <bool kUni>
-__device__ __forceinline__ uint32_t origin_x16(uint32_t w, int odd)
-{
-    if (kUni) return odd ? (w & 0x70000u) : ((w << 16) & 0x70000u);
-    return __builtin_amdgcn_perm(w, w, odd ? 0x0C020C0Cu : 0x0C000C0Cu);
-}
-template <bool kUni>
-__device__ __forceinline__ uint32_t origin_y16(uint32_t w, int odd)
-{
-    if (kUni) return odd ? ((w >> 8) & 0x70000u) : ((w << 8) & 0x70000u);
-    return __builtin_amdgcn_perm(w, w, odd ? 0x0C030C0Cu : 0x0C010C0Cu);
-}
-template <bool kUni>
-__device__ __forceinline__ uint32_t origin_yx(uint32_t w, int odd)
-{
-    if (kUni) return odd ? (((w >> 8) & 0x70000u) | ((w >> 16) & 7u)) : (((w << 8) & 0x70000u) | (w & 7u));
-    return __builtin_amdgcn_perm(w, w, odd ? 0x0C030C02u : 0x0C010C00u);
-}
+// Origin of the cell grid in step 2m + odd of a block, (y << 8) | x, from the
+// block's origin word m.
+__device__ __forceinline__ uint32_t origin_yx(uint32_t w, int odd) { return odd ? w >> 16 : w & 0xffffu; }
 
 // One sweep of blocks [b0, b0 + G) of the lattice described by `a`.
 //   kFixedB = 256: 256 x 256 blocks, G = 1, static geometry;
@@ -304,14 +308,29 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
     // Element e: tile row R = e >> 3 (band R >> lby, block row v = R mod By)
     // and its 32-site piece c = e & 7 (block c >> lwpr of the band, word
     // k = c mod wpr of the block row): consecutive lanes fill consecutive
-    // pieces of a tile row.
+    // pieces of a tile row.  A thread handles the same elements at the load and
+    // at the store.
     const int nrows = kFixedB ? kFixedB : (((G + (1 << lbpb) - 1) >> lbpb) << lby);
-    for (int e = tid; e < nrows * 8; e += kThreads) {
+    const size_t plane = (size_t)a.Ly * a.W;
+
+    // H0: the height of lattice site (0,0) moves by twice the change of the
+    // sigma_x count of its block row's prefix.  The thread holding a piece of
+    // that row counts the piece before the steps and after them.
+    const int g00 = a.blk00 - b0;
+    const bool has00 = (g00 >= 0 && g00 < G);  // uniform per workgroup
+    auto prefix00 = [&](int g, int v, int k, uint32_t nx) -> int {  // sigma_x = -1 bonds of the prefix in this piece
+        const int n = min(32, a.u00 - 32 * k);
+        if (g != g00 || v != a.v00 || n <= 0) return 0;
+        return __popc(nx & (~0u >> (32 - n)));
+    };
+    int pre00 = 0;
+
+    auto load_words = [&](int e, uint32_t w[4]) {
         const int c = e & 7, R = e >> 3;
         const int k = c & (wpr - 1);
         const int v = R & (By - 1);
         const int g = kFixedB ? 0 : (((R >> lby) << lbpb) | (c >> lwpr));
-        if (!kFixedB && g >= G) continue;  // the unused end of a last band
+        if (!kFixedB && g >= G) return;  // the unused end of a last band
         const int xs = kFixedB ? fxs : geo[3 * g];
         int y = (kFixedB ? fy0 : geo[3 * g + 1]) + v;
         if (y >= a.Ly) y -= a.Ly;
@@ -319,45 +338,56 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
         if (gw >= a.W) gw -= a.W;
         int gw1 = gw + 1;
         if (gw1 == a.W) gw1 = 0;
-        const uint32_t off = (uint32_t)(xs & 31);
         const uint32_t *r0 = a.src + (size_t)y * a.W;
-        const uint32_t *r1 = r0 + (size_t)a.Ly * a.W;
-        const uint32_t bxw = ~funnel(r0[gw1], r0[gw], off);  // nx bits
-        const uint32_t byw = ~funnel(r1[gw1], r1[gw], off);
+        const uint32_t *r1 = r0 + plane;
+        w[0] = r0[gw];
+        w[1] = r0[gw1];
+        w[2] = r1[gw];
+        w[3] = r1[gw1];
+    };
+    auto stage_words = [&](int e, const uint32_t w[4]) {
+        const int c = e & 7, R = e >> 3;
+        const int k = c & (wpr - 1);
+        const int v = R & (By - 1);
+        const int g = kFixedB ? 0 : (((R >> lby) << lbpb) | (c >> lwpr));
+        if (!kFixedB && g >= G) return;
+        const uint32_t off = (uint32_t)((kFixedB ? fxs : geo[3 * g]) & 31);
+        const uint32_t bxw = ~funnel(w[1], w[0], off);  // nx bits
+        const uint32_t byw = ~funnel(w[3], w[2], off);
+        if (has00) pre00 += prefix00(g, v, k, bxw);
         uint32_t d[8];
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            // nx in bit 0, ny in bit 1 of each byte (the bit fields are
-            // disjoint, so OR composes them); copies in bits 3 and 4
-            const uint32_t sxy = spread4((bxw >> (4 * m)) & 15u) |
-                                 (__umul24((byw >> (4 * m)) & 15u, 0x408102u) & 0x02020202u);
-            d[m] = sxy | (sxy << 3);
-        }
+        expand32(__brev(bxw), __brev(byw), d);
         if (v == 0) {  // row v = 0 is the block border (few waves take this)
 #pragma unroll
-            for (int m = 0; m < 8; ++m) d[m] |= 0x04040404u;
+            for (int m = 0; m < 8; ++m) d[m] |= 0x01010101u * kDead;
         }
-        if (k == 0) d[0] |= 4u;  // column u = 0 is the block border
+        if (k == 0) d[0] |= kDead;  // column u = 0 is the block border
         uint4 *dst = reinterpret_cast<uint4 *>(smem + kPitch + R * kPitch + 32 * c);
         dst[0] = uint4{d[0], d[1], d[2], d[3]};
         dst[1] = uint4{d[4], d[5], d[6], d[7]};
+    };
+    if (kFixedB) {
+        // all loads of the thread's elements in flight at once
+        constexpr int kEl = kFixedB ? kFixedB * 8 / kThreads : 1;
+        uint32_t w[kEl][4];
+#pragma unroll
+        for (int i = 0; i < kEl; ++i) load_words(tid + i * kThreads, w[i]);
+#pragma unroll
+        for (int i = 0; i < kEl; ++i) stage_words(tid + i * kThreads, w[i]);
+    } else {
+        for (int e = tid; e < nrows * 8; e += kThreads) {
+            uint32_t w[4] = {0, 0, 0, 0};
+            load_words(e, w);
+            stage_words(e, w);
+        }
     }
     __syncthreads();
-
-    // H0: the block holding lattice site (0,0), if it is in this group
-    const int g00 = a.blk00 - b0;
-    const bool has00 = (g00 >= 0 && g00 < G);  // uniform per workgroup
-    int pre00 = 0;
-    if (has00) {
-        if (tid == 0) pre00 = row_prefix_bx(smem + kPitch + tile_base(g00) + (a.v00 << 8), a.u00);
-        __syncthreads();  // no step may flip that row before it is counted
-    }
 
     // ---- the thread's cells ----------------------------------------------
     // A cell beyond the group gets zero masks and tile 0, so its site is
     // always (0,0) of block 0, a dead-border site: its attempt is a no-op.
     const uint32_t mk = ((uint32_t)(By - 1) << 8) | (uint32_t)(Bx - 1);  // (v << 8) | u
-    uint32_t cxo[kCpt], cyo[kCpt], mkj[kCpt], gbase[kCpt], cid[kCpt], bidj[kCpt];
+    uint32_t clo[kCpt], chi[kCpt], mkj[kCpt], cid[kCpt], bidj[kCpt];
     uint32_t gj[kCpt];
     uint32_t opreg[kCpt];
 #pragma unroll
@@ -382,16 +412,28 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
         const bool live = g < G;
         cid[j] = (uint32_t)c;
         bidj[j] = (uint32_t)block_id(live ? g : 0);
-        // dead cell borders: the active sites start one in from the origin
-        cxo[j] = (uint32_t)((c % ncx) * 8 + (kDelayed ? 0 : 1));
-        cyo[j] = (uint32_t)((c / ncx) * 8 + (kDelayed ? 0 : 1));
+        // First site of the cell, (row << 8) | column (dead cell borders: the
+        // active sites start one in), as its low seven bits and its top bit per
+        // byte: sums of the low part with a site and an origin stay below 256 in
+        // each byte, and the top bits are added modulo 256 by an XOR.
+        const uint32_t first = ((uint32_t)((c / ncx) * 8) << 8 | (uint32_t)((c % ncx) * 8)) + (kDelayed ? 0u : 0x0101u);
+        clo[j] = first & 0x7F7Fu;
         mkj[j] = live ? mk : 0u;
-        gbase[j] = live ? tile_base(g) : 0u;
+        // the block's place in the tile, in bits that mk masks off
+        chi[j] = live ? (first & 0x8080u) | tile_base(g) : 0u;
         gj[j] = live ? (uint32_t)g : 0u;
         opreg[j] = opk[(live ? g : 0) * kOpkStride + (tid & 31)];
     }
-    const uint32_t fixed_tbl = (a.Tp != 0 ? (1u << 24) : 0u) | (a.Tq != 0 ? (1u << 3) : 0u);
-    (void)fixed_tbl;
+    // Candidate bytes and acceptance: a minimum moves if its draw r < Tp, a
+    // maximum if r < Tq, as r <= T - 1 in 32 bits; a kind that never moves
+    // (T = 0) has no candidate byte.
+    const uint32_t min_byte = (kMode == kGrowth || a.Tp != 0) ? 0u : 0xFFu;
+    const uint32_t max_byte = a.Tq != 0 ? kTop : 0xFFu;
+    const uint32_t tp1 = (uint32_t)(a.Tp - 1), tq1 = (uint32_t)(a.Tq - 1);
+    (void)min_byte;
+    (void)max_byte;
+    (void)tp1;
+    (void)tq1;
 
     // Site words of 8 steps come from one Philox call per cell; the call for
     // the next 8 steps is spread over the current ones (about 1.25 rounds
@@ -402,11 +444,16 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
         const Ctr4 r = philox10_dev(Ctr4{a.s, bidj[j], cid[j], kTagSite}, a.k0, a.k1);
         sw[j][0] = r.x; sw[j][1] = r.y; sw[j][2] = r.z; sw[j][3] = r.w;
     }
-    // neighbour bytes: a lane whose site cannot move keeps the bytes it read
-    // last (any value gives no move, see below), so no per-step reset is needed
-    uint32_t lv[kCpt], dv[kCpt];
+    // Acceptance draws of 4 steps come from one Philox call per cell, computed
+    // the same way one call ahead.
+    uint32_t aw[kCpt][4];
+    if (kDrawAccept) {
 #pragma unroll
-    for (int j = 0; j < kCpt; ++j) lv[j] = dv[j] = 0;
+        for (int j = 0; j < kCpt; ++j) {
+            const Ctr4 r = philox10_dev(Ctr4{a.s, bidj[j], cid[j], kTagAccept}, a.k0, a.k1);
+            aw[j][0] = r.x; aw[j][1] = r.y; aw[j][2] = r.z; aw[j][3] = r.w;
+        }
+    }
 
     // The 64 steps.  kUni: the 64 lanes of a wave share a block, so the
     // origin words are read across lanes into scalar registers; otherwise
@@ -419,75 +466,63 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
 #pragma unroll
             for (int j = 0; j < kCpt; ++j) opv[j] = opk[gj[j] * kOpkStride];
         }
-        for (int gs = 0; gs < kSteps / 8; ++gs) {
+        // steps 8 gs .. 8 gs + 7; kMore: another group follows (its Philox calls are made here)
+        auto step_group = [&](int gs, auto more) __attribute__((always_inline)) {
+            constexpr bool kMore = decltype(more)::value;
             Ctr4 nxt[kCpt];
 #pragma unroll
             for (int j = 0; j < kCpt; ++j)
                 nxt[j] = Ctr4{a.s, bidj[j], ((uint32_t)(gs + 1) << 16) | cid[j], kTagSite};
-            uint32_t aw[kCpt][4];
+            Ctr4 nxa[kCpt];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = gs * 8 + e;
                 if (kDrawAccept && (e & 3) == 0) {
 #pragma unroll
-                    for (int j = 0; j < kCpt; ++j) {
-                        const Ctr4 r = philox10_dev(
-                            Ctr4{a.s, bidj[j], ((uint32_t)(k >> 2) << 16) | cid[j], kTagAccept}, a.k0,
-                            a.k1);
-                        aw[j][0] = r.x; aw[j][1] = r.y; aw[j][2] = r.z; aw[j][3] = r.w;
-                    }
+                    for (int j = 0; j < kCpt; ++j)
+                        nxa[j] = Ctr4{a.s, bidj[j], ((uint32_t)((k >> 2) + 1) << 16) | cid[j], kTagAccept};
                 }
-                // all reads of the step first: the cells' byte sets are disjoint.
-                // For a site byte that is neither 0 nor 0x1B the low three bits
-                // of the site byte already rule out a move, whatever the
-                // neighbour bytes hold.
-                uint32_t off[kCpt], sv[kCpt], phs[kCpt];
+                // all reads of the step first: the cells' byte sets are disjoint
+                uint32_t off[kCpt], sv[kCpt];
+                bool on_col[kCpt], on_row[kCpt];  // delayed borders: site in the cell's left column, bottom row
 #pragma unroll
                 for (int j = 0; j < kCpt; ++j) {
                     if (kUni && (e & 1) == 0) opv[j] = (uint32_t)__builtin_amdgcn_readlane((int)opreg[j], k >> 1);
                     const uint32_t h16 = (e & 1) ? (sw[j][e >> 1] >> 16) : (sw[j][e >> 1] & 0xffffu);
-                    uint32_t o;
+                    uint32_t site;  // (row << 8) | column within the cell
                     if (kDelayed) {
-                        // site i = floor(64 h / 2^16) of the 8 x 8 cell: a = i mod 8,
-                        // b = i div 8; phase 0 bulk, 1 edge (one of a, b zero),
-                        // 2 corner
-                        const uint32_t ca = (h16 >> 10) & 7u, cb = h16 >> 13;
-                        phs[j] = (uint32_t)(ca == 0u) + (uint32_t)(cb == 0u);
-                        // row in the high half, column in the low half (no
-                        // carry between them); one byte permute takes both
-                        // mod 256 into (row << 8) | column
-                        const uint32_t Y = ((cb << 16) | ca) + ((cyo[j] << 16) | cxo[j]) +
-                                           origin_yx<kUni>(opv[j], e & 1);
-                        o = __builtin_amdgcn_perm(Y, Y, 0x0C0C0200u);
+                        // site i = floor(64 h / 2^16) of the 8 x 8 cell: column
+                        // i mod 8, row i div 8
+                        const uint32_t i = h16 >> 10;
+                        site = (i | (i << 5)) & 0x0707u;
+                        on_col[j] = (i & 7u) == 0u;
+                        on_row[j] = i < 8u;
                     } else {
                         // Active site i = floor(49 h / 2^16) of the 7 x 7 (row-major),
                         // split as i = 7 q + a without a division: with 7 h = q 2^16 + r,
                         // q = floor(7 h / 2^16) = i div 7 and a = floor(7 r / 2^16) = i mod 7.
-                        // Y = 7 h + (row base << 16) keeps r in its low half, so
-                        // bits 16..23 of Y and X are the row and the column mod
-                        // 256; one byte permute packs them into (row << 8) | column
-                        const uint32_t Y = __umul24(h16, 7u) + (cyo[j] << 16) + origin_y16<kUni>(opv[j], e & 1);
-                        const uint32_t X =
-                            __umul24(Y & 0xffffu, 7u) + (cxo[j] << 16) + origin_x16<kUni>(opv[j], e & 1);
-                        o = __builtin_amdgcn_perm(Y, X, 0x0C0C0602u);
+                        // One byte permute packs bits 16..23 of the two products.
+                        const uint32_t Y = __umul24(h16, 7u);
+                        const uint32_t X = __umul24(Y & 0xffffu, 7u);
+                        site = __builtin_amdgcn_perm(Y, X, 0x0C0C0602u);
                     }
-                    // smaller blocks: row and column mod the block sides, then
-                    // the block's place in the tile (disjoint bits)
-                    if (!kFixedB) o = (o & mkj[j]) | gbase[j];
-                    off[j] = o;
+                    // plus the grid's origin and the cell's first site, row and
+                    // column mod the block sides, at the block's place in the tile
+                    const uint32_t o = site + origin_yx(opv[j], e & 1) + clo[j];
+                    off[j] = kFixedB ? (o ^ chi[j]) : __builtin_amdgcn_bitop3_b32(o, mkj[j], chi[j], 0x6A);
                     sv[j] = smem[off[j] + kPitch];
                     // behind the site read of a pair's second step: the next
                     // pair's origin word (the last pair reads its own again)
                     if (!kUni && (e & 1) == 1) opv[j] = opk[gj[j] * kOpkStride + min((k >> 1) + 1, kSteps / 2 - 1)];
                 }
                 // While the reads are in flight: this step's share of the next
-                // Philox call, pinned here so that it is not sunk to its use.
+                // Philox calls, pinned here so that it is not sunk to its use.
                 // It is filler work: at low wave priority, so that waves whose
                 // step chain can go on (towards the step barrier) issue first.
                 __builtin_amdgcn_s_setprio(0);
-                if (gs + 1 < kSteps / 8) {
 #pragma unroll
-                    for (int j = 0; j < kCpt; ++j) {
+                for (int j = 0; j < kCpt; ++j) {
+                    if (kMore) {
                         switch (e) {  // rounds 0,1 | 1,2 | 2,3 | 3,5 | 5,6 | 6,7 | 7,8 | 8,10
                         case 0: philox_rounds<0, 1>(nxt[j], a.k0, a.k1); break;
                         case 1: philox_rounds<1, 2>(nxt[j], a.k0, a.k1); break;
@@ -500,8 +535,33 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
                         }
                         asm volatile("" : "+v"(nxt[j].x), "+v"(nxt[j].y), "+v"(nxt[j].z), "+v"(nxt[j].w));
                     }
+                    if (kDrawAccept && (kMore || e < 4)) {
+                        switch (e & 3) {  // the call for steps k + 4 ..
+                        case 0: philox_rounds<0, 3>(nxa[j], a.k0, a.k1); break;
+                        case 1: philox_rounds<3, 5>(nxa[j], a.k0, a.k1); break;
+                        case 2: philox_rounds<5, 8>(nxa[j], a.k0, a.k1); break;
+                        default: philox_rounds<8, 10>(nxa[j], a.k0, a.k1); break;
+                        }
+                        asm volatile("" : "+v"(nxa[j].x), "+v"(nxa[j].y), "+v"(nxa[j].z), "+v"(nxa[j].w));
+                    }
+                }
+                bool up[kCpt], down[kCpt];  // the acceptance draws
+                if (kDrawAccept) {
+#pragma unroll
+                    for (int j = 0; j < kCpt; ++j) {
+                        up[j] = aw[j][e & 3] <= tp1;
+                        down[j] = aw[j][e & 3] <= tq1;
+                    }
                 }
                 __builtin_amdgcn_s_setprio(2);
+                // Only a site at a local minimum (byte 0) or maximum (kTop) whose
+                // draw accepts can move; only those lanes read the two neighbour
+                // bytes.
+                auto candidate = [&](int j) -> bool {
+                    if (kMode == kGrowth) return sv[j] == 0u;
+                    if (kMode == kFixed) return (sv[j] == min_byte) | (sv[j] == max_byte);
+                    return ((sv[j] == min_byte) & up[j]) | ((sv[j] == max_byte) & down[j]);
+                };
                 if (kDelayed) {
                     // Three phases.  Within one, attempted sites are never nearest
                     // neighbours.  Bulk sites are not diagonal neighbours either
@@ -519,66 +579,73 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
                     // cell's corner; for a corner, its own cell's.  A cell
                     // attempts one site per step, so no move of an earlier
                     // phase touches the byte of a later-phase site.
+                    bool cand[kCpt];
+#pragma unroll
+                    for (int j = 0; j < kCpt; ++j) cand[j] = candidate(j);
 #pragma unroll
                     for (int ph = 0; ph < 3; ++ph) {
 #pragma unroll
                         for (int j = 0; j < kCpt; ++j) {
-                            if (phs[j] != (uint32_t)ph) continue;
-                            const uint32_t s0 = sv[j];
-                            if (s0 != 0u && (kMode == kGrowth || s0 != 0x1Bu)) continue;
+                            const bool now = ph == 0 ? !(on_col[j] || on_row[j]) : ph == 1 ? on_col[j] != on_row[j] : on_col[j] && on_row[j];
+                            if (!(cand[j] && now)) continue;
                             uint32_t l0 = smem[off[j] + kPitch - 1];
                             uint32_t d0 = smem[off[j]];
-                            // the loads zero-extend; as in the dead-border steps,
-                            // keep the code generator from re-masking the bytes
+                            // the loads zero-extend; keep the code generator from
+                            // re-masking the bytes
                             asm volatile("" : "+v"(l0), "+v"(d0));
-                            const uint32_t r = kDrawAccept ? aw[j][e & 3] : 0u;
-                            if (!move_accepted<kMode>(s0, l0, d0, fixed_tbl, r, a.Tp, a.Tq)) continue;
+                            if (!move_allowed<kMode>(sv[j], l0, d0)) continue;
                             if (ph == 1) {
-                                xor_byte(smem, off[j] + kPitch, 0x1Bu);
-                                xor_byte(smem, off[j] + kPitch - 1, 0x09u);
-                                xor_byte(smem, off[j], 0x12u);
+                                xor_byte(smem, off[j] + kPitch, kTop);
+                                xor_byte(smem, off[j] + kPitch - 1, kNx);
+                                xor_byte(smem, off[j], kNy);
                             } else {
-                                smem[off[j] + kPitch] = (uint8_t)(s0 ^ 0x1Bu);
-                                smem[off[j] + kPitch - 1] = (uint8_t)(l0 ^ 0x09u);
-                                smem[off[j]] = (uint8_t)(d0 ^ 0x12u);
+                                smem[off[j] + kPitch] = (uint8_t)(sv[j] ^ kTop);
+                                smem[off[j] + kPitch - 1] = (uint8_t)(l0 ^ kNx);
+                                smem[off[j]] = (uint8_t)(d0 ^ kNy);
                             }
                         }
                         __syncthreads();
                     }
-                    continue;
-                }
+                } else {
+                    uint32_t lv[kCpt], dv[kCpt];
+                    bool cand[kCpt];
 #pragma unroll
-                for (int j = 0; j < kCpt; ++j) {
-                    // the loads zero-extend; keep the code generator from
-                    // re-narrowing the bytes (it would add masking operations)
-                    asm volatile("" : "+v"(sv[j]));
-                    // Only a site at a local minimum (byte 0) or maximum (0x1B)
-                    // can move; only those lanes read the two neighbour bytes,
-                    // which roughly halves the LDS read traffic of a step.
-                    const bool cand = (sv[j] == 0u) || (kMode != kGrowth && sv[j] == 0x1Bu);
-                    if (cand) {
-                        lv[j] = smem[off[j] + kPitch - 1];
-                        dv[j] = smem[off[j]];
+                    for (int j = 0; j < kCpt; ++j) {
+                        asm volatile("" : "+v"(sv[j]));
+                        cand[j] = candidate(j);
+                        if (cand[j]) {
+                            lv[j] = smem[off[j] + kPitch - 1];
+                            dv[j] = smem[off[j]];
+                        }
                     }
-                    asm volatile("" : "+v"(lv[j]), "+v"(dv[j]));
-                }
 #pragma unroll
-                for (int j = 0; j < kCpt; ++j) {
-                    const uint32_t r = kDrawAccept ? aw[j][e & 3] : 0u;
-                    if (move_accepted<kMode>(sv[j], lv[j], dv[j], fixed_tbl, r, a.Tp, a.Tq)) {
-                        // a growth flip only ever turns 0 (minimum) into 0x1B
-                        smem[off[j] + kPitch] = (kMode == kGrowth) ? (uint8_t)0x1Bu : (uint8_t)(sv[j] ^ 0x1Bu);
-                        smem[off[j] + kPitch - 1] = (uint8_t)(lv[j] ^ 0x09u);
-                        smem[off[j]] = (uint8_t)(dv[j] ^ 0x12u);
+                    for (int j = 0; j < kCpt; ++j) {
+                        if (!cand[j]) continue;
+                        asm volatile("" : "+v"(lv[j]), "+v"(dv[j]));
+                        if (move_allowed<kMode>(sv[j], lv[j], dv[j])) {
+                            // a growth flip only ever turns 0 (minimum) into kTop
+                            smem[off[j] + kPitch] = (kMode == kGrowth) ? (uint8_t)kTop : (uint8_t)(sv[j] ^ kTop);
+                            smem[off[j] + kPitch - 1] = (uint8_t)(lv[j] ^ kNx);
+                            smem[off[j]] = (uint8_t)(dv[j] ^ kNy);
+                        }
+                    }
+                    __syncthreads();
+                }
+                if (kDrawAccept && (e & 3) == 3) {
+#pragma unroll
+                    for (int j = 0; j < kCpt; ++j) {
+                        aw[j][0] = nxa[j].x; aw[j][1] = nxa[j].y; aw[j][2] = nxa[j].z; aw[j][3] = nxa[j].w;
                     }
                 }
-                __syncthreads();
             }
 #pragma unroll
             for (int j = 0; j < kCpt; ++j) {
                 sw[j][0] = nxt[j].x; sw[j][1] = nxt[j].y; sw[j][2] = nxt[j].z; sw[j][3] = nxt[j].w;
             }
-        }
+        };
+        // the last group apart: no branch inside a step
+        for (int gs = 0; gs < kSteps / 8 - 1; ++gs) step_group(gs, std::true_type{});
+        step_group(kSteps / 8 - 1, std::false_type{});
     };
     run_steps(std::integral_constant<bool, kFixedB != 0 || !kLaneOrg>{});
 
@@ -586,36 +653,23 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
     // priority, behind the steps of a co-resident workgroup
     __builtin_amdgcn_s_setprio(0);
 
-    if (has00 && tid == 0) {
-        const int post00 = row_prefix_bx(smem + kPitch + tile_base(g00) + (a.v00 << 8), a.u00);
-        *a.h0 += 2 * (int64_t)(post00 - pre00);
-    }
-
     // ---- LDS -> HBM: bytes -> bits, aligned into the other copy -----------
     // (elements as in the load above)
-    for (int e = tid; e < nrows * 8; e += kThreads) {
+    auto store_piece = [&](int e) {
         const int c = e & 7, R = e >> 3;
         const int k = c & (wpr - 1);
         const int v = R & (By - 1);
         const int g = kFixedB ? 0 : (((R >> lby) << lbpb) | (c >> lwpr));
-        if (!kFixedB && g >= G) continue;
+        if (!kFixedB && g >= G) return;
         const int bi = kFixedB ? fbi : geo[3 * g + 2];
         int y = (kFixedB ? fy0 : geo[3 * g + 1]) + v;
         if (y >= a.Ly) y -= a.Ly;
         const uint4 *src = reinterpret_cast<const uint4 *>(smem + kPitch + R * kPitch + 32 * c);
         const uint4 q0 = src[0], q1 = src[1];
         const uint32_t d[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-        uint32_t bxw = 0, byw = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {  // byte b of the word: sites 8b .. 8b+7
-            const uint32_t lo = d[2 * b], hi = d[2 * b + 1];
-            const uint32_t xb = gather4(hi & 0x01010101u, 0x80402010u,
-                                        gather4(lo & 0x01010101u, 0x08040201u, 0u));
-            const uint32_t yb = gather4((hi >> 1) & 0x01010101u, 0x80402010u,
-                                        gather4((lo >> 1) & 0x01010101u, 0x08040201u, 0u));
-            bxw |= xb << (8 * b);
-            byw |= yb << (8 * b);
-        }
+        uint32_t bxw, byw;
+        pack32(d, bxw, byw);
+        if (has00) pre00 -= prefix00(g, v, k, bxw);
         const size_t col = (size_t)bi * wpr + k;
         if (kOneCopy) {
             // One lattice copy: the block goes back where it was read from,
@@ -657,9 +711,9 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
                 put_bits(rx + gl, nx >> (32 - off), (1u << off) - 1u);
                 put_bits(ry + gl, ny >> (32 - off), (1u << off) - 1u);
             }
-            continue;
+            return;
         }
-        uint32_t *w0 = a.dst + (size_t)y * a.W + col, *w1 = a.dst + ((size_t)a.Ly + y) * a.W + col;
+        uint32_t *w0 = a.dst + (size_t)y * a.W + col, *w1 = w0 + plane;
         if (kStoreThrough) {
             __hip_atomic_store(w0, ~bxw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(w1, ~byw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -667,7 +721,16 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
             *w0 = ~bxw;  // back to sigma = +1 bits
             *w1 = ~byw;
         }
+    };
+    if (kFixedB) {
+#pragma unroll
+        for (int i = 0; i < (kFixedB ? kFixedB * 8 / kThreads : 1); ++i) store_piece(tid + i * kThreads);
+    } else {
+        for (int e = tid; e < nrows * 8; e += kThreads) store_piece(e);
     }
+    // few lanes of one workgroup (a piece's change is at most 32 bonds)
+    if (has00 && pre00 != 0)
+        atomicAdd(reinterpret_cast<unsigned long long *>(a.h0), (unsigned long long)(2 * (int64_t)pre00));
 }
 
 }  // namespace core
