@@ -39,6 +39,7 @@ struct okpz_sim {
     int threads;  // sweep workgroup size (execution mapping only)
     int32_t cell_borders;  // OKPZ_CELLS_DEAD or OKPZ_CELLS_DELAYED
     void *psd_mem;  // spectrum scratch, allocated by the first okpz_psd
+    int cus;        // the device's compute units
     int device;     // device current at creation, whose static scratch okpz_psd_noalloc uses
 };
 
@@ -69,6 +70,9 @@ int hip_fail(hipError_t e, const char *what)
     } while (0)
 
 constexpr size_t kAlign = 256;
+// Sweeps of one launch of a single-workgroup lattice: about a millisecond, so that
+// a long call still shares the device with other streams.
+constexpr int kChainSweeps = 64;
 size_t align_up(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
 
 size_t plane_bytes(int64_t Lx, int64_t Ly) { return 2 * (size_t)Ly * (size_t)(Lx / 32) * 4; }
@@ -214,6 +218,11 @@ int make_sim(okpz_sim **out, int64_t Lx, int64_t Ly, double p, double q, uint64_
     if (de != hipSuccess) {
         delete s;
         return hip_fail(de, "hipGetDevice");
+    }
+    const hipError_t ce = hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device);
+    if (ce != hipSuccess) {
+        delete s;
+        return hip_fail(ce, "hipDeviceGetAttribute");
     }
     static_scratch_setup(s->device);
     int rc = alloc_state(s, dev_buf, bytes, stream);
@@ -417,6 +426,24 @@ int okpz_sweep(okpz_sim *s, int64_t n_mcs)
                          (s->Tq == 0 || s->Tq == (uint64_t(1) << 32));
     a.need_accept_draws = trivial ? 0 : 1;
     a.delayed_cells = s->cell_borders == OKPZ_CELLS_DELAYED ? 1 : 0;
+    a.in_place = s->copies == 1 ? 1 : 0;
+    a.cus = s->cus;
+    if (okpz::sweep_chain_ok(a, s->threads)) {
+        for (int64_t done = 0; done < n_mcs;) {
+            const int n = (int)std::min<int64_t>(n_mcs - done, kChainSweeps);
+            a.src = s->buf[s->cur];
+            a.dst = s->buf[s->cur ^ 1];
+            a.ox_src = s->ox;
+            a.s = (uint32_t)s->t;
+            HIP_TRY(okpz::launch_sweep_chain(a, n, s->stream));
+            s->cur ^= n & 1;
+            int32_t sy;
+            okpz::block_shift(s->k0, s->k1, (uint32_t)(s->t + n - 1), s->g, &s->ox, &sy);
+            s->t += n;
+            done += n;
+        }
+        return OKPZ_OK;
+    }
     for (int64_t n = 0; n < n_mcs; ++n) {
         const uint32_t sw = (uint32_t)s->t;
         int32_t sx, sy;
@@ -428,7 +455,6 @@ int okpz_sweep(okpz_sim *s, int64_t n_mcs)
         a.src = s->buf[s->cur];
         a.dst = s->buf[s->cur ^ (s->copies - 1)];
         a.ox_src = s->ox;
-        a.in_place = s->copies == 1 ? 1 : 0;
         a.sx = sx;
         a.sy = sy;
         a.s = sw;

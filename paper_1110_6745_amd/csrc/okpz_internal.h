@@ -73,6 +73,8 @@ struct SweepLaunch {
     // every block row (launch_sweep sets them; blk00 is then numbered among
     // them, -1 if the block holding site (0,0) is not one of them)
     int32_t col0, col_step, ncol;
+    // compute units the launch has to itself (0: it shares the device)
+    int32_t cus;
 };
 
 // Block shift of sweep s (host side; the kernel uses the same values).
@@ -84,5 +86,10 @@ hipError_t launch_init(uint32_t *planes, int32_t Ly, int32_t W, hipStream_t st);
 // result does not depend on it)
 hipError_t launch_sweep(const SweepLaunch &a, int threads, hipStream_t st);
 bool sweep_threads_ok(int threads);
+// Whether the lattice's blocks fit one workgroup, so that several sweeps in a row
+// can be one launch: launch_sweep_chain runs n >= 1 of them, a.s being the first,
+// copy a.src the state before it and a.dst the other copy (two copies only).
+bool sweep_chain_ok(const SweepLaunch &a, int threads);
+hipError_t launch_sweep_chain(const SweepLaunch &a, int n, hipStream_t st);
 
 }  // namespace okpz
