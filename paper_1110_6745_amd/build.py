@@ -11,7 +11,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["api.hip", "sweep.hip", "sweep_chain.hip", "width.hip", "psd.hip", "batch.hip"]
+SOURCES = ["api.hip", "sweep.hip", "sweep_chain.hip", "width.hip", "psd.hip", "batch.hip", "state_io.hip"]
 HOST_SOURCES = ["host_logic.cpp"]  # plain C++, no device code
 LIB = os.path.join(HERE, "libokpz.so")
 RESOURCES = os.path.join(HERE, "_build", "kernel_resources.json")

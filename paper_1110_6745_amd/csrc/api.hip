@@ -14,6 +14,7 @@
 #include "host_logic.h"
 #include "okpz_internal.h"
 #include "psd.h"
+#include "state_io.h"
 #include "width.h"
 
 struct okpz_sim {
@@ -39,6 +40,7 @@ struct okpz_sim {
     int threads;  // sweep workgroup size (execution mapping only)
     int32_t cell_borders;  // OKPZ_CELLS_DEAD or OKPZ_CELLS_DELAYED
     void *psd_mem;  // spectrum scratch, allocated by the first okpz_psd
+    void *io_mem;   // staging of lattice transfers, allocated by the first one
     int cus;        // the device's compute units
     int device;     // device current at creation, whose static scratch okpz_psd_noalloc uses
 };
@@ -143,6 +145,7 @@ void release(okpz_sim *s)
     if (!s) return;
     (void)hipStreamSynchronize(s->stream);
     if (s->psd_mem) (void)hipFree(s->psd_mem);
+    if (s->io_mem) (void)hipFree(s->io_mem);
     if (s->own_mem && s->mem) (void)hipFree(s->mem);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
@@ -248,43 +251,53 @@ int launch_flat(okpz_sim *s)
     return OKPZ_OK;
 }
 
+// The handle's staging buffer for lattice transfers (at most 16 MiB, kept until
+// okpz_free), or nullptr where no device memory is left.
+void *io_buffer(okpz_sim *s)
+{
+    if (!s->io_mem && hipMalloc(&s->io_mem, okpz::io_bytes(s->Lx, s->Ly)) != hipSuccess) {
+        (void)hipGetLastError();
+        s->io_mem = nullptr;
+    }
+    return s->io_mem;
+}
+
+okpz::LatticeView view_of(const okpz_sim *s, int copy, int32_t ox)
+{
+    return okpz::LatticeView{s->buf[copy], (int32_t)s->Lx, (int32_t)s->Ly, s->W, ox};
+}
+
+// Whether the slope field check's counts (state_io.h) say that a copy is valid.
+bool planes_valid(const int64_t state[3], int64_t Lx, int64_t Ly)
+{
+    return state[0] == 0 && 2 * state[1] == Lx && 2 * state[2] == Ly;
+}
+
 // physical column x of stored copy with offset ox: stored column (x - ox) mod Lx
 inline int64_t stored_col(int64_t x, int32_t ox, int64_t Lx) { return ((x - ox) % Lx + Lx) % Lx; }
 
-int download_rows(okpz_sim *s, int64_t y0, int64_t n, std::vector<uint32_t> &pl0,
-                  std::vector<uint32_t> &pl1)
+// Rows as canonical bytes without device memory of their own (the staging buffer
+// could not be allocated): packed rows to the host, unpacked there.
+int get_rows_on_host(okpz_sim *s, int64_t y0, int64_t n, uint8_t *host)
 {
     const size_t W = (size_t)s->W;
-    pl0.resize(n * W);
-    pl1.resize(n * W);
-    HIP_TRY(hipStreamSynchronize(s->stream));
-    int64_t done = 0;
-    while (done < n) {
-        const int64_t y = (y0 + done) % s->Ly;
-        const int64_t run = std::min<int64_t>(n - done, s->Ly - y);
-        const uint32_t *src0 = s->buf[s->cur] + (size_t)y * W;
-        const uint32_t *src1 = s->buf[s->cur] + ((size_t)s->Ly + y) * W;
-        HIP_TRY(hipMemcpy(pl0.data() + done * W, src0, run * W * 4, hipMemcpyDeviceToHost));
-        HIP_TRY(hipMemcpy(pl1.data() + done * W, src1, run * W * 4, hipMemcpyDeviceToHost));
-        done += run;
+    const int64_t Lx = s->Lx;
+    std::vector<uint32_t> px(W), py(W);
+    for (int64_t r = 0; r < n; ++r) {
+        const int64_t y = (y0 + r) % s->Ly;
+        HIP_TRY(hipMemcpy(px.data(), s->buf[s->cur] + (size_t)y * W, W * 4, hipMemcpyDeviceToHost));
+        HIP_TRY(hipMemcpy(py.data(), s->buf[s->cur] + ((size_t)s->Ly + y) * W, W * 4, hipMemcpyDeviceToHost));
+        for (int64_t x = 0; x < Lx; ++x) {
+            const int64_t c = stored_col(x, s->ox, Lx);
+            const uint32_t bx = (px[c >> 5] >> (c & 31)) & 1u, by = (py[c >> 5] >> (c & 31)) & 1u;
+            host[r * Lx + x] = (uint8_t)(bx | (by << 1));
+        }
     }
     return OKPZ_OK;
 }
 
-void unpack_rows(const okpz_sim *s, int64_t n, const std::vector<uint32_t> &pl0,
-                 const std::vector<uint32_t> &pl1, uint8_t *host)
-{
-    const int64_t Lx = s->Lx;
-    const size_t W = (size_t)s->W;
-    for (int64_t r = 0; r < n; ++r)
-        for (int64_t x = 0; x < Lx; ++x) {
-            const int64_t c = stored_col(x, s->ox, Lx);
-            const uint32_t bx = (pl0[r * W + (c >> 5)] >> (c & 31)) & 1u;
-            const uint32_t by = (pl1[r * W + (c >> 5)] >> (c & 31)) & 1u;
-            host[r * Lx + x] = (uint8_t)(bx | (by << 1));
-        }
-}
-
+// A canonical lattice already known to be valid, packed on the host into copy 0
+// (one lattice copy, or no staging buffer).
 int upload_lattice(okpz_sim *s, const uint8_t *host)
 {
     const size_t W = (size_t)s->W;
@@ -299,6 +312,33 @@ int upload_lattice(okpz_sim *s, const uint8_t *host)
     HIP_TRY(hipMemcpy(s->buf[0], planes.data(), planes.size() * 4, hipMemcpyHostToDevice));
     s->cur = 0;
     s->ox = 0;
+    return OKPZ_OK;
+}
+
+// The same through the device: bytes in chunks of rows into the staging buffer,
+// packed into the copy that the next sweep would overwrite and tested there, which
+// then becomes the current one.  *valid is 0, and the state as it was, for a lattice
+// that is no slope field.
+int upload_lattice_checked(okpz_sim *s, const uint8_t *host, void *io, int *valid)
+{
+    const int to = s->cur ^ 1;
+    const okpz::LatticeView v = view_of(s, to, 0);
+    const int64_t most = (int64_t)(okpz::io_bytes(s->Lx, s->Ly) / (size_t)s->Lx);
+    HIP_TRY(okpz::launch_clear_check_state(s->d_out, s->stream));
+    for (int64_t y = 0; y < s->Ly; y += most) {
+        const int64_t n = std::min(most, s->Ly - y);
+        HIP_TRY(hipMemcpyAsync(io, host + (size_t)y * s->Lx, (size_t)n * s->Lx, hipMemcpyHostToDevice, s->stream));
+        HIP_TRY(okpz::launch_pack_rows(v, (int32_t)y, (int32_t)n, static_cast<uint8_t *>(io), s->d_out, s->stream));
+    }
+    HIP_TRY(okpz::launch_check_planes(v, s->d_out, s->stream));
+    int64_t state[3];
+    HIP_TRY(hipMemcpyAsync(state, s->d_out, sizeof state, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    *valid = planes_valid(state, s->Lx, s->Ly) ? 1 : 0;
+    if (*valid) {
+        s->cur = to;
+        s->ox = 0;
+    }
     return OKPZ_OK;
 }
 
@@ -590,10 +630,11 @@ int okpz_get_rows(okpz_sim *s, int64_t y0, int64_t nrows, uint8_t *host, size_t 
     if (nrows < 0 || nrows > s->Ly) return fail(OKPZ_EINVAL, "nrows out of range");
     if (bytes < (size_t)(nrows * s->Lx)) return fail(OKPZ_EINVAL, "host buffer too small");
     y0 = ((y0 % s->Ly) + s->Ly) % s->Ly;
-    std::vector<uint32_t> p0, p1;
-    int rc = download_rows(s, y0, nrows, p0, p1);
-    if (rc != OKPZ_OK) return rc;
-    unpack_rows(s, nrows, p0, p1, host);
+    void *io = io_buffer(s);
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    if (!io) return get_rows_on_host(s, y0, nrows, host);
+    HIP_TRY(okpz::download_rows(view_of(s, s->cur, s->ox), y0, nrows, host, io, okpz::io_bytes(s->Lx, s->Ly),
+                                s->stream));
     return OKPZ_OK;
 }
 
@@ -610,11 +651,19 @@ int okpz_set_lattice(okpz_sim *s, const uint8_t *host, size_t bytes, int64_t H0,
     if (t < 0 || t >= (int64_t(1) << 32)) return fail(OKPZ_EINVAL, "t out of range");
     if (!okpz::host::valid_h0(H0))
         return fail(OKPZ_EINVAL, "height of site (0,0) must be even (h = x + y mod 2)");
-    std::string why;
-    if (!okpz::host::valid_slope_field(host, s->Lx, s->Ly, why))
-        return fail(OKPZ_EINVAL, "not a valid slope field: %s", why.c_str());
-    int rc = upload_lattice(s, host);
-    if (rc != OKPZ_OK) return rc;
+    void *io = s->copies == 2 ? io_buffer(s) : nullptr;
+    int valid = 0;
+    if (io) {
+        const int rc = upload_lattice_checked(s, host, io, &valid);
+        if (rc != OKPZ_OK) return rc;
+    }
+    if (!valid) {  // not tested yet, or to say what is wrong
+        std::string why;
+        if (!okpz::host::valid_slope_field(host, s->Lx, s->Ly, why))
+            return fail(OKPZ_EINVAL, "not a valid slope field: %s", why.c_str());
+        const int rc = upload_lattice(s, host);
+        if (rc != OKPZ_OK) return rc;
+    }
     hipLaunchKernelGGL(set_h0_kernel, dim3(1), dim3(1), 0, s->stream, s->d_h0, H0);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(s->stream));
@@ -661,22 +710,37 @@ int okpz_load(okpz_sim **out, const void *buf, size_t bytes)
     CkptHeader h;
     const uint32_t *planes = nullptr;
     std::string why;
-    if (!okpz::host::parse_checkpoint(buf, bytes, &h, &planes, why))
+    if (!okpz::host::parse_checkpoint_header(buf, bytes, &h, &planes, why))
         return fail(OKPZ_EINVAL, "%s", why.c_str());
     const size_t pb = plane_bytes(h.Lx, h.Ly);
+    // a bad lattice is refused as such, also where no device state can be made
+    auto bad_planes = [&]() { return !okpz::host::parse_checkpoint(buf, bytes, &h, &planes, why); };
     okpz_sim *s = nullptr;
     int rc = make_sim(&s, h.Lx, h.Ly, h.p, h.q, h.seed, nullptr, 0, nullptr, h.copies == 1 ? 1 : 2);
-    if (rc != OKPZ_OK) return rc;
-    hipError_t e = hipMemcpy(s->buf[0], planes, pb, hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        release(s);
-        return hip_fail(e, "hipMemcpy(checkpoint)");
+    if (rc != OKPZ_OK) {
+        if (bad_planes()) return fail(OKPZ_EINVAL, "%s", why.c_str());
+        return rc;
     }
-    hipLaunchKernelGGL(set_h0_kernel, dim3(1), dim3(1), 0, s->stream, s->d_h0, h.H0);
-    e = hipStreamSynchronize(s->stream);
+    // the slope field test runs on the uploaded planes; only a failed one is
+    // repeated on the host, for its message
+    int64_t state[3] = {1, 0, 0};
+    hipError_t e = hipMemcpyAsync(s->buf[0], planes, pb, hipMemcpyHostToDevice, s->stream);
+    if (e == hipSuccess) e = okpz::launch_clear_check_state(s->d_out, s->stream);
+    if (e == hipSuccess) e = okpz::launch_check_planes(view_of(s, 0, 0), s->d_out, s->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(state, s->d_out, sizeof state, hipMemcpyDeviceToHost, s->stream);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(set_h0_kernel, dim3(1), dim3(1), 0, s->stream, s->d_h0, h.H0);
+        e = hipGetLastError();
+    }
+    const hipError_t se = hipStreamSynchronize(s->stream);
+    if (e == hipSuccess) e = se;
     if (e != hipSuccess) {
         release(s);
         return hip_fail(e, "restore");
+    }
+    if (!planes_valid(state, h.Lx, h.Ly) && bad_planes()) {
+        release(s);
+        return fail(OKPZ_EINVAL, "%s", why.c_str());
     }
     s->cur = 0;
     s->ox = h.ox;

@@ -36,6 +36,7 @@
 
 #include "host_logic.h"
 #include "okpz.h"
+#include "state_io.h"
 #include "sweep_core.h"
 #include "width.h"
 #include "width_core.h"
@@ -417,6 +418,8 @@ struct okpz_batch {
     std::vector<JobDesc> desc;
     double m;
     void *mem = nullptr;
+    void *io_mem = nullptr;  // staging of okpz_batch_get_lattice, allocated by the first one
+    size_t io_size = 0;
     JobDesc *d_desc = nullptr;
     JobState *d_state = nullptr;
     Control *d_ctl = nullptr;
@@ -1037,6 +1040,22 @@ int okpz_batch_get_lattice(okpz_batch *b, int32_t job, uint8_t *host, size_t byt
     if (bytes < (size_t)d.Lx * d.Ly) return bfail(OKPZ_EINVAL, "host buffer too small");
     JobState st;
     BHIP(hipMemcpy(&st, b->d_state + job, sizeof st, hipMemcpyDeviceToHost));
+    const okpz::LatticeView v{d.buf[st.cur], d.Lx, d.Ly, d.W, st.ox};
+    if (!b->io_mem) {  // for the largest job of the batch, at most 16 MiB
+        size_t size = 0;
+        for (const JobDesc &o : b->desc) size = std::max(size, okpz::io_bytes(o.Lx, o.Ly));
+        if (hipMalloc(&b->io_mem, size) == hipSuccess) {
+            b->io_size = size;
+        } else {
+            (void)hipGetLastError();
+            b->io_mem = nullptr;
+        }
+    }
+    if (b->io_mem) {
+        BHIP(okpz::download_rows(v, 0, d.Ly, host, b->io_mem, b->io_size, b->stream));
+        return OKPZ_OK;
+    }
+    // no device memory left for the staging: unpacked on the host
     std::vector<uint32_t> pl(2 * (size_t)d.Ly * d.W);
     BHIP(hipMemcpy(pl.data(), d.buf[st.cur], pl.size() * 4, hipMemcpyDeviceToHost));
     for (int64_t y = 0; y < d.Ly; ++y)
@@ -1054,6 +1073,7 @@ int okpz_batch_free(okpz_batch *b)
     if (!b) return OKPZ_OK;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     if (b->mem) (void)hipFree(b->mem);
+    if (b->io_mem) (void)hipFree(b->io_mem);
     if (b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
     return OKPZ_OK;
@@ -1190,16 +1210,12 @@ int retire(okpz_server *sv, ServeJob &J, double t, bool cancelled = false)
             st.ox = J.ox;
             st.cur = J.cur;
         }
-        std::vector<uint32_t> pl(2 * (size_t)d.Ly * d.W);
-        BHIP(hipMemcpy(pl.data(), st.cur ? d.buf[1] : d.buf[0], pl.size() * 4, hipMemcpyDeviceToHost));
+        // between quanta every job stands at a whole sweep, so the other copy is
+        // free to stage the bytes (a quarter of the lattice at a time)
         J.lattice.resize((size_t)d.Lx * d.Ly);
-        for (int64_t y = 0; y < d.Ly; ++y)
-            for (int64_t x = 0; x < d.Lx; ++x) {
-                const int64_t c = ((x - st.ox) % d.Lx + d.Lx) % d.Lx;
-                const uint32_t bx = (pl[(size_t)y * d.W + (c >> 5)] >> (c & 31)) & 1u;
-                const uint32_t by = (pl[((size_t)d.Ly + y) * d.W + (c >> 5)] >> (c & 31)) & 1u;
-                J.lattice[y * d.Lx + x] = (uint8_t)(bx | (by << 1));
-            }
+        const okpz::LatticeView v{st.cur ? d.buf[1] : d.buf[0], d.Lx, d.Ly, d.W, st.ox};
+        BHIP(okpz::download_rows(v, 0, d.Ly, J.lattice.data(), st.cur ? d.buf[0] : d.buf[1],
+                                 (size_t)d.Lx * d.Ly / 4, sv->stream));
     }
     BHIP(hipFree(J.mem));
     J.mem = nullptr;

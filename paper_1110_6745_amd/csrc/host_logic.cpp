@@ -85,8 +85,8 @@ bool valid_packed_planes(const uint32_t *planes, int64_t Lx, int64_t Ly, std::st
 
 size_t packed_plane_bytes(int64_t Lx, int64_t Ly) { return 2 * (size_t)Ly * (size_t)(Lx / 32) * 4; }
 
-bool parse_checkpoint(const void *buf, size_t bytes, CkptHeader *h, const uint32_t **planes,
-                      std::string &why)
+bool parse_checkpoint_header(const void *buf, size_t bytes, CkptHeader *h, const uint32_t **planes,
+                             std::string &why)
 {
     if (bytes < sizeof(CkptHeader)) {
         why = "checkpoint truncated";
@@ -112,9 +112,18 @@ bool parse_checkpoint(const void *buf, size_t bytes, CkptHeader *h, const uint32
         why = "checkpoint truncated";
         return false;
     }
-    // the planes follow the header; an unaligned buffer is checked on a copy
-    const char *p = static_cast<const char *>(buf) + sizeof(CkptHeader);
-    *planes = reinterpret_cast<const uint32_t *>(p);
+    // the planes follow the header
+    *planes = reinterpret_cast<const uint32_t *>(static_cast<const char *>(buf) + sizeof(CkptHeader));
+    return true;
+}
+
+bool parse_checkpoint(const void *buf, size_t bytes, CkptHeader *h, const uint32_t **planes,
+                      std::string &why)
+{
+    if (!parse_checkpoint_header(buf, bytes, h, planes, why)) return false;
+    const size_t pb = packed_plane_bytes(h->Lx, h->Ly);
+    // an unaligned buffer is checked on a copy
+    const char *p = reinterpret_cast<const char *>(*planes);
     std::vector<uint32_t> copy;
     const uint32_t *view = *planes;
     if (reinterpret_cast<uintptr_t>(p) % alignof(uint32_t)) {

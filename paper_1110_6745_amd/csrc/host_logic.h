@@ -49,6 +49,11 @@ struct CkptHeader {
 
 size_t packed_plane_bytes(int64_t Lx, int64_t Ly);
 
+// Parse and check a checkpoint's header (fields in range, even H0) and size,
+// without looking at the stored planes.
+bool parse_checkpoint_header(const void *buf, size_t bytes, CkptHeader *h, const uint32_t **planes,
+                             std::string &why);
+
 // Parse and check a checkpoint buffer: header fields in range, size, even
 // H0 and a valid slope field in the stored planes.  On success *h holds the
 // header and *planes points at the stored planes inside buf (which need not

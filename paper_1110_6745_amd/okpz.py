@@ -298,9 +298,9 @@ class Sim:
     def save(self) -> bytes:
         n = _sz(0)
         _check(_lib.okpz_save(self._h, None, ctypes.byref(n)))
-        buf = ctypes.create_string_buffer(n.value)
-        _check(_lib.okpz_save(self._h, buf, ctypes.byref(n)))
-        return buf.raw[: n.value]
+        buf = np.empty(n.value, dtype=np.uint8)
+        _check(_lib.okpz_save(self._h, _vp(buf.ctypes.data), ctypes.byref(n)))
+        return buf[: n.value].tobytes()
 
     def set_threads(self, threads: int) -> None:
         _check(_lib.okpz_set_threads(self._h, int(threads)))
