@@ -40,6 +40,7 @@ struct okpz_sim {
     int threads;  // sweep workgroup size (execution mapping only)
     int32_t cell_borders;  // OKPZ_CELLS_DEAD or OKPZ_CELLS_DELAYED
     void *psd_mem;  // spectrum scratch, allocated by the first okpz_psd
+    int64_t *h_out; // pinned host memory that the width kernel writes its sums to
     void *io_mem;   // staging of lattice transfers, allocated by the first one
     int cus;        // the device's compute units
     int device;     // device current at creation, whose static scratch okpz_psd_noalloc uses
@@ -146,6 +147,7 @@ void release(okpz_sim *s)
     (void)hipStreamSynchronize(s->stream);
     if (s->psd_mem) (void)hipFree(s->psd_mem);
     if (s->io_mem) (void)hipFree(s->io_mem);
+    if (s->h_out) (void)hipHostFree(s->h_out);
     if (s->own_mem && s->mem) (void)hipFree(s->mem);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
@@ -511,11 +513,17 @@ int okpz_sweep(okpz_sim *s, int64_t n_mcs)
 static int measure(okpz_sim *s, __int128 *S1r, __int128 *S2r, int64_t *H0)
 {
     okpz::LatticeView v{s->buf[s->cur], (int32_t)s->Lx, (int32_t)s->Ly, s->W, s->ox};
-    HIP_TRY(okpz::launch_width(v, s->d_rows, s->d_out, s->stream));
+    // five words straight to the host: two copies of a few bytes cost as much as
+    // the kernel on a small lattice
+    if (!s->h_out && hipHostMalloc(reinterpret_cast<void **>(&s->h_out), 8 * sizeof(int64_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        s->h_out = nullptr;
+    }
     int64_t host[5];
-    HIP_TRY(hipMemcpyAsync(host, s->d_out, 4 * sizeof(int64_t), hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipMemcpyAsync(host + 4, s->d_h0, sizeof(int64_t), hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(okpz::launch_width(v, s->d_rows, s->d_h0, s->h_out ? s->h_out : s->d_out, -1, s->stream));
+    if (!s->h_out) HIP_TRY(hipMemcpyAsync(host, s->d_out, sizeof host, hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
+    if (s->h_out) std::memcpy(host, s->h_out, sizeof host);
     *S1r = (__int128)(((unsigned __int128)(uint64_t)host[1] << 64) | (uint64_t)host[0]);
     *S2r = (__int128)(((unsigned __int128)(uint64_t)host[3] << 64) | (uint64_t)host[2]);
     *H0 = host[4];

@@ -363,18 +363,6 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
     }
 }
 
-// One width sample of a job run with plain sweep launches: t, the 128-bit
-// sums from out[0..3] and H0, in the layout the persistent kernel writes.
-__global__ void record_sample_kernel(int64_t *sample, int32_t t, const int64_t *out,
-                                     const int64_t *h0)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        sample[0] = t;
-        for (int i = 0; i < 4; ++i) sample[1 + i] = out[i];
-        sample[5] = *h0;
-    }
-}
-
 // Flat zig-zag state h = (x+y) mod 2 in copy 0 of every job, H0 = 0.
 __global__ void init_jobs_kernel(const JobDesc *jobs, int32_t njobs)
 {
@@ -1333,13 +1321,10 @@ int run_grid(okpz_server *sv, ServeJob &J, int64_t stop)
         J.s += 1;
         if (J.next_sample < d.nsamp && J.times[J.next_sample] == J.s) {
             const okpz::LatticeView v{d.buf[J.cur], d.Lx, d.Ly, d.W, J.ox};
-            int64_t *out = d.rows + okpz::width_scratch_words(d.Ly);
-            e = okpz::launch_width(v, d.rows, out, sv->grid_stream);
+            // a sample is t, then what the width launch writes
+            e = okpz::launch_width(v, d.rows, d.h0, d.samples + 6 * (size_t)J.next_sample + 1, J.s,
+                                   sv->grid_stream);
             if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "serve width: %s", hipGetErrorString(e));
-            hipLaunchKernelGGL(okpz::batch::record_sample_kernel, dim3(1), dim3(64), 0,
-                               sv->grid_stream, d.samples + 6 * (size_t)J.next_sample, J.s, out,
-                               d.h0);
-            BHIP(hipGetLastError());
             ++J.next_sample;
         }
     }
