@@ -41,6 +41,7 @@ struct okpz_sim {
     int32_t cell_borders;  // OKPZ_CELLS_DEAD or OKPZ_CELLS_DELAYED
     void *psd_mem;  // spectrum scratch, allocated by the first okpz_psd
     int64_t *h_out; // pinned host memory that the width kernel writes its sums to
+    void *h_spec;   // pinned host memory for the spectra of short sides
     void *io_mem;   // staging of lattice transfers, allocated by the first one
     int cus;        // the device's compute units
     int device;     // device current at creation, whose static scratch okpz_psd_noalloc uses
@@ -148,6 +149,7 @@ void release(okpz_sim *s)
     if (s->psd_mem) (void)hipFree(s->psd_mem);
     if (s->io_mem) (void)hipFree(s->io_mem);
     if (s->h_out) (void)hipHostFree(s->h_out);
+    if (s->h_spec) (void)hipHostFree(s->h_spec);
     if (s->own_mem && s->mem) (void)hipFree(s->mem);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
@@ -161,6 +163,7 @@ constexpr size_t kStaticPsdBytes = size_t(24) << 20;
 constexpr int64_t kStaticPsdMaxSide = int64_t(1) << 17;
 static __device__ __align__(256) unsigned char scratch[kStaticPsdBytes];
 
+constexpr size_t kPinnedSpectra = size_t(1) << 20;
 constexpr int kMaxDevices = 64;
 std::mutex g_static_mu;
 void *g_static_ptr[kMaxDevices];     // device address of `scratch` per device
@@ -566,6 +569,31 @@ int okpz_w2(okpz_sim *s, double *w2)
     return OKPZ_OK;
 }
 
+// The two spectra, one after the other at spec on the device, to the host.
+static int copy_spectra(okpz_sim *s, const char *spec, double *sx, double *sy)
+{
+    const size_t bx = ((size_t)s->Lx / 2 + 1) * 8, by = ((size_t)s->Ly / 2 + 1) * 8;
+    // Up to a mebibyte in one copy to pinned memory: two copies to the caller's
+    // (pageable) arrays take about 60 us of a small lattice's call.
+    if (bx + by <= kPinnedSpectra) {
+        if (!s->h_spec && hipHostMalloc(&s->h_spec, bx + by) != hipSuccess) {
+            (void)hipGetLastError();
+            s->h_spec = nullptr;
+        }
+        if (s->h_spec) {
+            HIP_TRY(hipMemcpyAsync(s->h_spec, spec, bx + by, hipMemcpyDeviceToHost, s->stream));
+            HIP_TRY(hipStreamSynchronize(s->stream));
+            if (sx) std::memcpy(sx, s->h_spec, bx);
+            if (sy) std::memcpy(sy, static_cast<const char *>(s->h_spec) + bx, by);
+            return OKPZ_OK;
+        }
+    }
+    if (sx) HIP_TRY(hipMemcpyAsync(sx, spec, bx, hipMemcpyDeviceToHost, s->stream));
+    if (sy) HIP_TRY(hipMemcpyAsync(sy, spec + bx, by, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    return OKPZ_OK;
+}
+
 int okpz_psd(okpz_sim *s, double *sx, double *sy)
 {
     if (!s) return fail(OKPZ_EINVAL, "null handle");
@@ -578,15 +606,8 @@ int okpz_psd(okpz_sim *s, double *sx, double *sy)
         }
     }
     okpz::LatticeView v{s->buf[s->cur], (int32_t)s->Lx, (int32_t)s->Ly, s->W, s->ox};
-    HIP_TRY(okpz::launch_width_rows(v, s->d_rows, s->stream));
     HIP_TRY(okpz::launch_psd(v, p, s->d_rows, s->psd_mem, s->stream));
-    const double *spec =
-        reinterpret_cast<const double *>(static_cast<const char *>(s->psd_mem) + p.off_spec);
-    const size_t nx = (size_t)s->Lx / 2 + 1, ny = (size_t)s->Ly / 2 + 1;
-    if (sx) HIP_TRY(hipMemcpyAsync(sx, spec, nx * 8, hipMemcpyDeviceToHost, s->stream));
-    if (sy) HIP_TRY(hipMemcpyAsync(sy, spec + nx, ny * 8, hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipStreamSynchronize(s->stream));
-    return OKPZ_OK;
+    return copy_spectra(s, static_cast<const char *>(s->psd_mem) + p.off_spec, sx, sy);
 }
 
 int okpz_psd_noalloc(okpz_sim *s, double *sx, double *sy)
@@ -605,14 +626,8 @@ int okpz_psd_noalloc(okpz_sim *s, double *sx, double *sy)
     void *mem = static_scratch(s->device, &se);
     if (!mem) return hip_fail(se, "hipGetSymbolAddress(scratch)");
     okpz::LatticeView v{s->buf[s->cur], (int32_t)s->Lx, (int32_t)s->Ly, s->W, s->ox};
-    HIP_TRY(okpz::launch_width_rows(v, s->d_rows, s->stream));
     HIP_TRY(okpz::launch_psd(v, p, s->d_rows, mem, s->stream));
-    const double *spec = reinterpret_cast<const double *>(static_cast<const char *>(mem) + p.off_spec);
-    const size_t nx = (size_t)s->Lx / 2 + 1, ny = (size_t)s->Ly / 2 + 1;
-    if (sx) HIP_TRY(hipMemcpyAsync(sx, spec, nx * 8, hipMemcpyDeviceToHost, s->stream));
-    if (sy) HIP_TRY(hipMemcpyAsync(sy, spec + nx, ny * 8, hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipStreamSynchronize(s->stream));
-    return OKPZ_OK;
+    return copy_spectra(s, static_cast<const char *>(mem) + p.off_spec, sx, sy);
 }
 
 int okpz_time(const okpz_sim *s, int64_t *t)

@@ -340,9 +340,7 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
             uint32_t *lut = reinterpret_cast<uint32_t *>(smem + 20 * 1024);
             core::width_lut_build(lut);
             __syncthreads();
-            // one word per lane: the narrow form keeps the kernel's registers
-            // down (a 1024 x 1024 lattice's rows are 32 words, one pass)
-            for (int y = wave; y < jd.Ly; y += nwave) core::width_row<1>(v, y, lane, lut, jd.rows);
+            for (int y = wave; y < jd.Ly; y += nwave) core::width_row(v, y, lane, lut, jd.rows);
             __syncthreads();  // rows are read back by other waves of this workgroup (same CU)
             core::width_combine(jd.rows, jd.Lx, jd.Ly, s_out, reinterpret_cast<int64_t *>(smem));
             if (tid == 0) {

@@ -8,115 +8,208 @@
 // that drop out of every n > 0,
 //   X(x) = sum_{l<x} (2 c(l) - Ly),  c(l) = number of rows with sigma_x(l,y) = +1,
 //   Y(y) = Lx G(y) + sum_x P_y(x).
-// So the surface is reduced exactly, in integers, to two profiles: a column
-// popcount of the sigma_x plane (one pass over N/8 bytes) and the per-row sums
-// the width pass already makes.  Each profile, minus its mean, goes through a
-// radix-2 decimation-in-frequency FFT in fp64: global passes while a
-// butterfly's span exceeds the LDS tile, then one LDS-resident pass per tile;
-// the output stays in bit-reversed order and the spectrum kernel reads it so.
-// A side that is not a power of two goes through Bluestein's chirp-z form
-// (Bluestein 1970): with c_j = exp(-i pi j^2 / n), X_k = c_k sum_j (x_j c_j)
-// conj(c_{k-j}), a convolution done with power-of-two transforms of length
-// M >= 2n - 1 (forward stages, a pointwise product in bit-reversed order, and
-// the forward stages undone in reverse order, which returns natural order).
+// Both are linear in the sigma_x bits, so one pass over that plane (N/8 bytes)
+// gives the column counts and the row sums, exactly, in integers.  Each profile,
+// minus its mean, goes through a radix-2 decimation-in-frequency FFT in fp64; its
+// stages are done three or four at a time in registers: first the stages that
+// span more than an LDS tile, then the rest of each tile in LDS.  The output stays
+// in bit-reversed order and the squares are written from there.  A side that is not
+// a power of two goes through Bluestein's chirp-z form (Bluestein 1970): with
+// c_j = exp(-i pi j^2 / n), X_k = c_k sum_j (x_j c_j) conj(c_{k-j}), a convolution
+// done with power-of-two transforms of length M >= 2n - 1 (forward stages, a
+// pointwise product in bit-reversed order, and the forward stages undone in reverse
+// order, which returns natural order); |c_k| = 1 drops out of the spectrum.  The two
+// axes share every launch where the scratch holds both.
+//
+// What bounds it: the pass over the plane from 32768^2 on (65536^2: 537 MB in 128 us,
+// 4.2 TB/s, bound by the latency of a wavefront's row sums; a row pass of the width
+// kernels and a column pass took 178 + 98 us and their sums 31), below that the chain of
+// four to six launches: 8160 x 4064, both sides through Bluestein, 60 us per call (330 us
+// with one launch per stage of 27 us tiles and serial sums over up to 254 parts).
 #include "psd.h"
 #include "width_core.h"
 
 namespace okpz {
 namespace {
 
-constexpr int kCountThreads = 256;
-constexpr int kScanThreads = 1024;
+constexpr int kPlaneThreads = 512;
+constexpr int kPlaneWaves = kPlaneThreads / 64;
+constexpr int kStripWords = 256;          // words of a row a wavefront takes: four per lane
+constexpr int kStripCols = 32 * kStripWords;
+constexpr int kGroupRows = 8;             // rows per carry-save group
+constexpr int kMaxWaveRows = 255 * kGroupRows;  // byte lanes count up to 255 groups
+constexpr int kPlaneTarget = 512;         // workgroups of the plane pass
 constexpr int kProfThreads = 256;
-constexpr int kFftThreads = 256;
-constexpr int kTile = 4096;          // complex fp64 values per LDS tile (64 KiB)
-constexpr int kTargetThreads = 1 << 18;
+constexpr int kFftThreads = 512;
+constexpr int kWideThreads = 256;
+constexpr int kTile = 4096;               // complex fp64 values per LDS tile
+constexpr int kTileLog = 12;
+constexpr int kWideLog = 4;               // stages of one pass over the whole transform
 
 // carry-save adder on 32 bit positions at once: a + b + c = 2 h + l
 __device__ __forceinline__ void csa(uint32_t &h, uint32_t &l, uint32_t a, uint32_t b, uint32_t c)
 {
-    const uint32_t u = a ^ b;
-    h = (a & b) | (u & c);
-    l = u ^ c;
+    h = __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);  // majority
+    l = __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// Column popcount of the sigma_x plane.  Thread (chunk, word column wc)
-// counts bit by bit over rows [chunk R, chunk R + R) with bit-sliced
-// counters: ones/twos/fours/eights hold the count modulo 16 of each of the
-// 32 columns, every 16 rows the carry out ("sixteens") goes into byte-lane
-// counters, which spill into 16-bit lanes every 255 groups.  Writes
-// partial[chunk * Lx + 32 wc + b] in stored-column order.
-__global__ __launch_bounds__(kCountThreads) void colcount_kernel(const uint32_t *plane, int32_t Ly,
-                                                                 int32_t W, int32_t R, int32_t nch,
-                                                                 int32_t *partial)
+// Sum over the wavefront, valid in lane 63.
+__device__ __forceinline__ int32_t wave_sum63(int32_t x)
 {
-    const int64_t t = (int64_t)blockIdx.x * kCountThreads + threadIdx.x;
-    if (t >= (int64_t)W * nch) return;
-    const int wc = (int)(t % W), ch = (int)(t / W);
-    const int y0 = ch * R, y1 = min(Ly, y0 + R);
-    const uint32_t *col = plane + wc;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast 15, 31
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
 
-    uint32_t ones = 0, twos = 0, fours = 0, eights = 0;
-    uint32_t acc[8], lo[8], hi[8];
+// One pass over the sigma_x plane.  Workgroup (strip, chunk) takes 256 word columns
+// and p.R rows, a wavefront p.R / kPlaneWaves of them, a lane four words of a row.
+// Columns: eight rows at a time go through a carry-save adder tree whose carry
+// out is counted in byte lanes; partial[chunk * Lx + stored column] gets the sigma_x =
+// +1 bonds of the chunk.  Rows, with E the strip's end: rowpart[strip * Ly + y] =
+// {sum of sigma(c) (E - 1 - c), d + 65536 q} with d the strip's sum of sigma and q its
+// part before the stored column xs0 of physical column 0 (|d|, |q| <= 8192).
+// A bit's weight within its word is read off five masked popcounts.
+// kVec: W is a multiple of four (16-byte loads, every lane has four words or none).
+// The next eight rows are in flight while eight are counted (sixteen left two waves per
+// SIMD for registers, three hide more).
+template <bool kVec>
+__global__ __launch_bounds__(kPlaneThreads, kVec ? 4 : 3) void plane_kernel(LatticeView v, int32_t R, int32_t *partial, int2 *rowpart)
+{
+    // counts of a lane's 128 columns, column j of lane l at 65 j + l: neither the
+    // lanes' sums nor the ordered read meet in a bank
+    __shared__ uint32_t cols[128 * 65];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int i = threadIdx.x; i < 128 * 65; i += kPlaneThreads) cols[i] = 0;
+    const int strip = blockIdx.x, k0 = strip * kStripWords + 4 * lane;
+    const int nw = max(0, min(4, v.W - k0));
+    const int E = min(v.Lx, (strip + 1) * kStripCols);
+    const int xs0 = (v.Lx - v.ox) % v.Lx;
+    const int before = xs0 - strip * kStripCols;  // columns of the strip before xs0
+    uint32_t mask[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = lo[j] = hi[j] = 0u;
-    auto spill = [&]() {
+    for (int t = 0; t < 4; ++t) {
+        const int n = before - 128 * lane - 32 * t;
+        mask[t] = n <= 0 ? 0u : n >= 32 ? ~0u : (1u << n) - 1u;
+    }
+    const bool split = before > 0 && before < kStripCols;
+    int nbefore = 0;  // columns of this lane before xs0
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            lo[j] += acc[j] & 0x00FF00FFu;
-            hi[j] += (acc[j] >> 8) & 0x00FF00FFu;
-            acc[j] = 0u;
+    for (int t = 0; t < 4; ++t) nbefore += t < nw ? __popc(mask[t]) : 0;
+
+    const int rw = R / kPlaneWaves;
+    const int ya = min(v.Ly, (int)blockIdx.y * R + wave * rw), yb = min(v.Ly, ya + rw);
+    uint32_t ones[4], twos[4], fours[4], acc[4][8];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        ones[t] = twos[t] = fours[t] = 0u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[t][j] = 0u;
+    }
+    // (rows and words beyond the ends are read from inside, and zeroed before use)
+    const uint32_t *word0 = v.planes + (kVec ? min(k0, v.W - 4) : 0);
+    auto load = [&](int y0, uint32_t w[kGroupRows][4]) {
+#pragma unroll
+        for (int i = 0; i < kGroupRows; ++i) {
+            const uint32_t *p = word0 + (size_t)min(y0 + i, yb - 1) * v.W;
+            if (kVec) {
+                const uint4 q = *reinterpret_cast<const uint4 *>(p);
+                w[i][0] = q.x; w[i][1] = q.y; w[i][2] = q.z; w[i][3] = q.w;
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) w[i][t] = p[min(k0 + t, v.W - 1)];
+            }
         }
     };
-    int groups = 0;
-    for (int y = y0; y < y1; y += 16) {
-        uint32_t w[16];
+    auto count = [&](int y0, uint32_t w[kGroupRows][4]) {
+        if (y0 + kGroupRows > yb) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) w[i] = (y + i < y1) ? col[(size_t)(y + i) * W] : 0u;
-        uint32_t twosA, twosB, foursA, foursB, eightsA, eightsB, sixteens;
-        csa(twosA, ones, ones, w[0], w[1]);
-        csa(twosB, ones, ones, w[2], w[3]);
-        csa(foursA, twos, twos, twosA, twosB);
-        csa(twosA, ones, ones, w[4], w[5]);
-        csa(twosB, ones, ones, w[6], w[7]);
-        csa(foursB, twos, twos, twosA, twosB);
-        csa(eightsA, fours, fours, foursA, foursB);
-        csa(twosA, ones, ones, w[8], w[9]);
-        csa(twosB, ones, ones, w[10], w[11]);
-        csa(foursA, twos, twos, twosA, twosB);
-        csa(twosA, ones, ones, w[12], w[13]);
-        csa(twosB, ones, ones, w[14], w[15]);
-        csa(foursB, twos, twos, twosA, twosB);
-        csa(eightsB, fours, fours, foursA, foursB);
-        csa(sixteens, eights, eights, eightsA, eightsB);
+            for (int i = 0; i < kGroupRows; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += (sixteens >> j) & 0x01010101u;
-        if (++groups == 255) {
-            spill();
-            groups = 0;
+                for (int t = 0; t < 4; ++t) w[i][t] = y0 + i < yb ? w[i][t] : 0u;
+        }
+        if (!kVec) {
+#pragma unroll
+            for (int i = 0; i < kGroupRows; ++i)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) w[i][t] = t < nw ? w[i][t] : 0u;
+        }
+        // rows
+#pragma unroll
+        for (int i = 0; i < kGroupRows; ++i) {
+            int32_t n[4], J = 0;  // set bits per word; sum of their places within the word
+#pragma unroll
+            for (int t = 0; t < 4; ++t) n[t] = __popc(w[i][t]);
+            auto place = [&](uint32_t m) {
+                J <<= 1;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) J += __popc(w[i][t] & m);
+            };
+            place(0xFFFF0000u);
+            place(0xFF00FF00u);
+            place(0xF0F0F0F0u);
+            place(0xCCCCCCCCu);
+            place(0xAAAAAAAAu);
+            // sigma = 2 b - 1: sum of sigma (E - 1 - c) over the lane's words
+            const int32_t d = 2 * (n[0] + n[1] + n[2] + n[3]) - 32 * nw;
+            const int32_t far = 2 * (n[1] + 2 * n[2] + 3 * n[3]) - 32 * (nw * (nw - 1) / 2);  // sum of t d_t
+            const int32_t r = (E - 1 - 32 * k0) * d - 32 * far - (2 * J - 496 * nw);
+            int32_t pack = d;
+            if (split) {
+                int32_t q = -nbefore;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) q += 2 * __popc(w[i][t] & mask[t]);
+                pack += q << 16;
+            } else if (before > 0) {
+                pack += d << 16;
+            }
+            const int32_t rs = wave_sum63(!kVec || nw ? r : 0), ps = wave_sum63(!kVec || nw ? pack : 0);
+            if (lane == 63 && y0 + i < yb) rowpart[(size_t)strip * v.Ly + y0 + i] = make_int2(rs, ps);
+        }
+        // columns
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint32_t twosA, twosB, foursA, foursB, eights;
+            csa(twosA, ones[t], ones[t], w[0][t], w[1][t]);
+            csa(twosB, ones[t], ones[t], w[2][t], w[3][t]);
+            csa(foursA, twos[t], twos[t], twosA, twosB);
+            csa(twosA, ones[t], ones[t], w[4][t], w[5][t]);
+            csa(twosB, ones[t], ones[t], w[6][t], w[7][t]);
+            csa(foursB, twos[t], twos[t], twosA, twosB);
+            csa(eights, fours[t], fours[t], foursA, foursB);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[t][j] += (eights >> j) & 0x01010101u;
+        }
+    };
+    if (ya < yb) {
+        uint32_t w0[kGroupRows][4], w1[kGroupRows][4];
+        load(ya, w0);
+        for (int y = ya; y < yb; y += 2 * kGroupRows) {
+            load(y + kGroupRows, w1);
+            count(y, w0);
+            load(y + 2 * kGroupRows, w0);
+            if (y + kGroupRows < yb) count(y + kGroupRows, w1);
         }
     }
-    spill();
-    int32_t c[32];
+    __syncthreads();  // cols is zero
 #pragma unroll
-    for (int b = 0; b < 32; ++b) {
-        const int j = b & 7, m = b >> 3;
-        const uint32_t lane16 = (((m & 1) ? hi[j] : lo[j]) >> (16 * (m >> 1))) & 0xffffu;
-        c[b] = (int32_t)(16 * lane16 + 8 * ((eights >> b) & 1u) + 4 * ((fours >> b) & 1u) +
-                         2 * ((twos >> b) & 1u) + ((ones >> b) & 1u));
+    for (int t = 0; t < 4; ++t) {
+        if (t >= nw || ya >= yb) continue;
+#pragma unroll
+        for (int b = 0; b < 32; ++b) {
+            const uint32_t n = 8 * ((acc[t][b & 7] >> (b & ~7)) & 0xffu) + 4 * ((fours[t] >> b) & 1u) +
+                               2 * ((twos[t] >> b) & 1u) + ((ones[t] >> b) & 1u);
+            atomicAdd(cols + 65 * (32 * t + b) + lane, n);
+        }
     }
-    int4 *out = reinterpret_cast<int4 *>(partial + (size_t)ch * 32 * W + 32 * (size_t)wc);
-#pragma unroll
-    for (int v = 0; v < 8; ++v) out[v] = make_int4(c[4 * v], c[4 * v + 1], c[4 * v + 2], c[4 * v + 3]);
-}
-
-__global__ void colsum_kernel(const int32_t *partial, int32_t nch, int32_t Lx, int32_t *cnt)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= Lx) return;
-    int32_t s = 0;
-    for (int ch = 0; ch < nch; ++ch) s += partial[(size_t)ch * Lx + c];
-    cnt[c] = s;
+    __syncthreads();
+    const int c0 = strip * kStripCols;
+    for (int c = threadIdx.x; c < E - c0; c += kPlaneThreads)
+        partial[(size_t)blockIdx.y * v.Lx + c0 + c] = (int32_t)cols[65 * (c & 127) + (c >> 7)];
 }
 
 // The profiles as scans of integer steps d(i):
@@ -124,156 +217,176 @@ __global__ void colsum_kernel(const int32_t *partial, int32_t nch, int32_t Lx, i
 // column profile X: d(l) = 2 c(stored column of l) - Ly, scale 1, e = 0;
 // row profile Y: d(y) = 2 sigma_y-bit(0,y) - 1, scale Lx, e(y) = the row's
 // sum of P.  Every v is an integer below 2^41 in magnitude, exact in fp64.
-// Three launches over blocks of kProfThreads values: block sums of d and of
-// v's contributions (sum_i v(i) = scale sum_j d(j) (n-1-j) + sum_j e(j)); one
-// workgroup scans the block sums and forms the mean; every block rescans its
-// values and writes v(i) - mean into the real parts of z.
-template <bool kRows>
-__device__ __forceinline__ int64_t profile_step(const int32_t *cnt, const int64_t *rows, int32_t Lx,
-                                                int32_t Ly, int32_t ox, int i)
-{
-    if (kRows) return 2 * rows[2 * (size_t)Ly + i] - 1;
-    int xs = i - ox;
-    if (xs < 0) xs += Lx;
-    return 2 * (int64_t)cnt[xs] - Ly;
-}
+// A block of kProfThreads values keeps its own prefix of d and two sums; the first
+// kernel of the transforms adds up the blocks' (Profile::offsets).
+struct Profile {
+    const int32_t *prefix;  // sum of d over the block's values before i
+    const int64_t *extra;   // e(i), or nullptr
+    const int64_t *blk;     // per block: sum of d, part of sum_i v(i)
+    int64_t scale;
+    int32_t n, nblk;
+};
+struct Profiles {
+    LatticeView v;
+    const int32_t *partial;
+    const int2 *rowpart;
+    int32_t nch;
+    int32_t *prefix[2];  // per axis (x, y)
+    int64_t *extra;
+    int64_t *blk[2];
+    int32_t nblk[2];
+};
 
-// blk[2 b] = sum of d over block b, blk[2 b + 1] = its part of sum_i v(i).
-template <bool kRows>
-__global__ __launch_bounds__(kProfThreads) void profile_sums_kernel(const int32_t *cnt,
-                                                                    const int64_t *rows, int32_t Lx,
-                                                                    int32_t Ly, int32_t ox,
-                                                                    int64_t *blk)
+__device__ __forceinline__ int side(const LatticeView &v, int axis) { return axis ? v.Ly : v.Lx; }
+
+// Blocks 0 .. nblk[0) take the columns, the others the rows: the parts of the plane
+// pass added up into d and e, the block's prefix of d, and its sums (sum_i v(i) =
+// scale sum_j d(j) (n-1-j) + sum_j e(j)).
+__global__ __launch_bounds__(kProfThreads) void profile_steps_kernel(Profiles p)
 {
     __shared__ int64_t lds[32];
-    const int n = kRows ? Ly : Lx;
-    const int64_t scale = kRows ? (int64_t)Lx : 1;
-    const int i = blockIdx.x * kProfThreads + threadIdx.x;
-    const int64_t d = i < n ? profile_step<kRows>(cnt, rows, Lx, Ly, ox, i) : 0;
-    const int64_t e = (kRows && i < n) ? rows[i] : 0;
-    const int64_t w = i < n ? scale * d * (int64_t)(n - 1 - i) + e : 0;
-    const __int128 D = core::block_sum_i128(d, lds);
-    const __int128 V = core::block_sum_i128(w, lds);
+    const LatticeView &v = p.v;
+    const int axis = (int)blockIdx.x >= p.nblk[0];
+    const int b = (int)blockIdx.x - (axis ? p.nblk[0] : 0);
+    const int n = side(v, axis), i = b * kProfThreads + threadIdx.x;
+    int64_t d = 0, e = 0;
+    if (i < n) {
+        if (axis == 0) {
+            int xs = i - v.ox;
+            if (xs < 0) xs += v.Lx;
+            int32_t c = 0;
+#pragma unroll 8
+            for (int ch = 0; ch < p.nch; ++ch) c += p.partial[(size_t)ch * v.Lx + xs];
+            d = 2 * (int64_t)c - v.Ly;
+        } else {
+            // sum of P = sum of Q - Lx Q(xs0), Q the stored-order prefix
+            int64_t q0 = 0;
+            for (int s = 0; s * kStripCols < v.Lx; ++s) {
+                const int2 r = p.rowpart[(size_t)s * v.Ly + i];
+                const int32_t ds = (int16_t)r.y;
+                e += r.x + (int64_t)ds * (v.Lx - min(v.Lx, (s + 1) * kStripCols));
+                q0 += (r.y - ds) >> 16;
+            }
+            e -= v.Lx * q0;
+            const int xs0 = (v.Lx - v.ox) % v.Lx;
+            const uint32_t w = v.planes[((size_t)v.Ly + i) * v.W + (xs0 >> 5)];
+            d = 2 * (int64_t)((w >> (xs0 & 31)) & 1u) - 1;
+            p.extra[i] = e;
+        }
+    }
+    const int64_t scale = axis ? v.Lx : 1;
+    int64_t D;
+    const int64_t pre = core::block_exclusive_scan(d, lds, &D);
+    if (i < n) p.prefix[axis][i] = (int32_t)pre;
+    const __int128 V = core::block_sum_i128(i < n ? scale * d * (int64_t)(n - 1 - i) + e : 0, lds);
     if (threadIdx.x == 0) {
-        blk[2 * (size_t)blockIdx.x] = (int64_t)D;
-        blk[2 * (size_t)blockIdx.x + 1] = (int64_t)V;
+        p.blk[axis][2 * (size_t)b] = D;
+        p.blk[axis][2 * (size_t)b + 1] = (int64_t)V;
     }
 }
 
-// In place: blk[2 b] becomes the exclusive prefix of the block sums of d;
-// blk[2 nb] receives the mean of v as the bits of a double.
-__global__ __launch_bounds__(kScanThreads) void profile_offsets_kernel(int64_t *blk, int32_t nb,
-                                                                       int32_t n)
+// Values of a profile for a workgroup: the blocks' offsets and the mean, worked out
+// once per workgroup (a launch of its own for this cost more: at most 4096 blocks).
+// off: LDS of at least nblk + 1 words; its rounding makes the mean move n = 0 only.
+// All threads; ends with a barrier.
+__device__ __forceinline__ void profile_offsets(const Profile &p, int64_t *off, int64_t *lds)
 {
-    __shared__ int64_t lds[32];
-    const int per = (nb + kScanThreads - 1) / kScanThreads;
-    const int b0 = min(nb, (int)threadIdx.x * per), b1 = min(nb, b0 + per);
+    const int per = (p.nblk + (int)blockDim.x - 1) / (int)blockDim.x;
+    const int b0 = min(p.nblk, (int)threadIdx.x * per), b1 = min(p.nblk, b0 + per);
     int64_t local = 0, vs = 0;
     for (int b = b0; b < b1; ++b) {
-        local += blk[2 * (size_t)b];
-        vs += blk[2 * (size_t)b + 1];
+        local += p.blk[2 * (size_t)b];
+        vs += p.blk[2 * (size_t)b + 1];
     }
     int64_t unused;
     int64_t run = core::block_exclusive_scan(local, lds, &unused);
-    const __int128 V = core::block_sum_i128(vs, lds);
     for (int b = b0; b < b1; ++b) {
-        const int64_t d = blk[2 * (size_t)b];
-        blk[2 * (size_t)b] = run;
-        run += d;
+        off[b] = run;
+        run += p.blk[2 * (size_t)b];
     }
-    if (threadIdx.x == 0) {
-        const double mean = (double)(int64_t)V / n;  // its rounding only moves n = 0
-        blk[2 * (size_t)nb] = __double_as_longlong(mean);
-    }
+    const __int128 V = core::block_sum_i128(vs, lds);
+    if (threadIdx.x == 0) off[p.nblk] = __double_as_longlong((double)(int64_t)V / p.n);
+    __syncthreads();
+}
+__device__ __forceinline__ double profile_value(const Profile &p, const int64_t *off, int i)
+{
+    const int64_t pre = off[i / kProfThreads] + p.prefix[i];
+    const int64_t v = p.scale * pre + (p.extra ? p.extra[i] : 0);
+    return (double)v - __longlong_as_double(off[p.nblk]);
+}
+constexpr int kMaxBlocks = (1 << 20) / kProfThreads;
+
+// ---- transforms ------------------------------------------------------------
+// One axis: the n values of a profile.  chirp: through Bluestein with the buffers A
+// and B of len = M values; otherwise len = n in z.
+struct Axis {
+    Profile prof;
+    double2 *z, *A, *B;
+    double *S;
+    double norm;  // 1 / (Lx Ly)
+    int32_t n, len, log2len;
+    bool chirp;
+};
+struct Axes {
+    Axis ax[2];
+};
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b)
+{
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-template <bool kRows>
-__global__ __launch_bounds__(kProfThreads) void profile_write_kernel(const int32_t *cnt,
-                                                                     const int64_t *rows,
-                                                                     int32_t Lx, int32_t Ly,
-                                                                     int32_t ox, const int64_t *blk,
-                                                                     int32_t nb, double2 *z)
+// z <- (z + w) at i, (z - w) e^{-i pi r / h} at i + h: one radix-2
+// decimation-in-frequency stage of span h on blocks of 2h values; tw = e^{-i pi r / h}.
+__device__ __forceinline__ void dif_butterfly(double2 &a, double2 &b, double2 tw)
 {
-    __shared__ int64_t lds[16];
-    const int n = kRows ? Ly : Lx;
-    const int64_t scale = kRows ? (int64_t)Lx : 1;
-    const int i = blockIdx.x * kProfThreads + threadIdx.x;
-    const int64_t d = i < n ? profile_step<kRows>(cnt, rows, Lx, Ly, ox, i) : 0;
-    int64_t unused;
-    const int64_t pre = blk[2 * (size_t)blockIdx.x] + core::block_exclusive_scan(d, lds, &unused);
-    if (i >= n) return;
-    const int64_t v = scale * pre + (kRows ? rows[i] : 0);
-    const double mean = __longlong_as_double(blk[2 * (size_t)nb]);
-    z[i] = make_double2((double)v - mean, 0.0);
-}
-
-// z <- (z + w) at i, (z - w) e^{-i pi (i mod 2h) / h} at i + h: one radix-2
-// decimation-in-frequency stage of span h on blocks of 2h values.
-__device__ __forceinline__ void dif_butterfly(double2 &a, double2 &b, int r, int h)
-{
-    double s, c;
-    sincospi(-(double)r / h, &s, &c);
     const double2 u = a, v = b;
     a = make_double2(u.x + v.x, u.y + v.y);
-    const double dx = u.x - v.x, dy = u.y - v.y;
-    b = make_double2(dx * c - dy * s, dx * s + dy * c);
+    b = cmul(make_double2(u.x - v.x, u.y - v.y), tw);
 }
 
 // The stage above undone without its factor 1/2: (a, b) <- (a + t, a - t),
 // t = b e^{+i pi r / h}.  All stages undone in reverse order turn the
 // bit-reversed transform of x back into n x in natural order, i.e. they
 // apply the unnormalised inverse DFT to a bit-reversed spectrum.
-__device__ __forceinline__ void dif_butterfly_undo(double2 &a, double2 &b, int r, int h)
+__device__ __forceinline__ void dif_butterfly_undo(double2 &a, double2 &b, double2 tw)
 {
-    double s, c;
-    sincospi((double)r / h, &s, &c);
-    const double2 t = make_double2(b.x * c - b.y * s, b.x * s + b.y * c);
+    const double2 t = cmul(b, make_double2(tw.x, -tw.y));
     const double2 u = a;
     a = make_double2(u.x + t.x, u.y + t.y);
     b = make_double2(u.x - t.x, u.y - t.y);
 }
 
-template <bool kUndo>
-__global__ __launch_bounds__(kFftThreads) void fft_stage_kernel(double2 *z, int32_t n, int32_t h)
+// e^{-i pi r / h}, h = 1 / inv a power of two (the product is exact).
+__device__ __forceinline__ double2 twiddle(int r, double inv)
 {
-    const int i = blockIdx.x * kFftThreads + threadIdx.x;  // butterfly index
-    if (i >= (n >> 1)) return;
-    const int r = i & (h - 1);
-    const int lo = ((i - r) << 1) + r;
-    double2 a = z[lo], b = z[lo + h];
-    if (kUndo)
-        dif_butterfly_undo(a, b, r, h);
-    else
-        dif_butterfly(a, b, r, h);
-    z[lo] = a;
-    z[lo + h] = b;
+    double s, c;
+    sincospi(-(double)r * inv, &s, &c);
+    return make_double2(c, s);
 }
 
-// The stages of spans T/2 .. 1 (undone: 1 .. T/2) of one contiguous tile of
-// T values, in LDS.
-template <bool kUndo>
-__global__ __launch_bounds__(kFftThreads) void fft_tile_kernel(double2 *z, int32_t T)
+// kLog stages in registers on the 2^kLog values x[m] at i + m step of a block of
+// 2^kLog step values; tw(r, l) = e^{-i pi r / h}, h = 2^l step.  A stage's twiddle
+// depends on m modulo its half only.
+template <int kLog, bool kUndo, class Tw>
+__device__ __forceinline__ void stages(double2 *x, int i, int step, Tw tw)
 {
-    __shared__ double2 tile[kTile];
-    double2 *g = z + (size_t)blockIdx.x * T;
-    for (int i = threadIdx.x; i < T; i += kFftThreads) tile[i] = g[i];
-    __syncthreads();
-    for (int k = 0; (1 << k) < T; ++k) {
-        const int h = kUndo ? (1 << k) : (T >> (k + 1));
-        for (int i = threadIdx.x; i < (T >> 1); i += kFftThreads) {
-            const int r = i & (h - 1);
-            const int lo = ((i - r) << 1) + r;
-            double2 a = tile[lo], b = tile[lo + h];
-            if (kUndo)
-                dif_butterfly_undo(a, b, r, h);
-            else
-                dif_butterfly(a, b, r, h);
-            tile[lo] = a;
-            tile[lo + h] = b;
+#pragma unroll
+    for (int q = 0; q < kLog; ++q) {
+        const int st = kUndo ? kLog - 1 - q : q;
+        const int half = (1 << kLog) >> (st + 1);
+#pragma unroll
+        for (int m = 0; m < half; ++m) {
+            const double2 w = tw(i + m * step, kLog - 1 - st);
+#pragma unroll
+            for (int g = 0; g < (1 << kLog); g += 2 * half) {
+                if (kUndo)
+                    dif_butterfly_undo(x[g + m], x[g + m + half], w);
+                else
+                    dif_butterfly(x[g + m], x[g + m + half], w);
+            }
         }
-        __syncthreads();
     }
-    for (int i = threadIdx.x; i < T; i += kFftThreads) g[i] = tile[i];
 }
 
 // c_j = exp(-i pi j^2 / n), the phase reduced exactly: j^2 mod 2n.
@@ -285,59 +398,185 @@ __device__ __forceinline__ double2 chirp(int64_t j, int32_t n)
     return make_double2(c, s);
 }
 
-// A = (x_j c_j, then zeros) and B = (conj(c_m) at m and M - m for m < n,
-// zeros between), both of length M.
-__global__ void chirp_kernel(const double2 *x, int32_t n, int32_t M, double2 *A, double2 *B)
+// The Bluestein operands at j: A = x_j c_j, then zeros; B = conj(c_m) at m and
+// M - m for m < n, zeros between.
+__device__ __forceinline__ double2 chirped(const Axis &a, const int64_t *off, int j)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= M) return;
-    if (j < n) {
-        const double2 c = chirp(j, n), v = x[j];
-        A[j] = make_double2(v.x * c.x - v.y * c.y, v.x * c.y + v.y * c.x);
-    } else {
-        A[j] = make_double2(0.0, 0.0);
+    if (j >= a.n) return make_double2(0.0, 0.0);
+    const double x = profile_value(a.prof, off, j);
+    const double2 c = chirp(j, a.n);
+    return make_double2(x * c.x, x * c.y);
+}
+__device__ __forceinline__ double2 chirp_filter(const Axis &a, int j)
+{
+    const int m = j < a.n ? j : (j > a.len - a.n ? a.len - j : -1);
+    if (m < 0) return make_double2(0.0, 0.0);
+    const double2 c = chirp(m, a.n);
+    return make_double2(c.x, -c.y);
+}
+
+// S(k) = |Z(k)|^2 / (Lx Ly); S(0) = 0 exactly (the mean is subtracted by definition).
+__device__ __forceinline__ void put_spectrum(const Axis &a, uint32_t k, double2 v, double norm)
+{
+    if (k <= (uint32_t)(a.n >> 1)) a.S[k] = k == 0 ? 0.0 : (v.x * v.x + v.y * v.y) * norm;
+}
+
+// A pass of kLog stages over whole transforms, blocks of L values (L = len for the
+// first forward and the last undone pass): thread i of a transform takes the values at
+// i0 + i + m L / 2^kLog.  The first forward pass makes its operands (off: the
+// profile's offsets), the last undone one writes the spectrum.
+template <int kLog, bool kUndo>
+__device__ __forceinline__ void wide_pass(const Axis &a, const int64_t *off, int which, int t, int32_t L)
+{
+    const int step = L >> kLog;
+    const int i = t & (step - 1);
+    const size_t base = (size_t)(t - i) << kLog;  // block's first value
+    double2 *buf = a.chirp ? (which ? a.B : a.A) : a.z;
+    double2 x[1 << kLog];
+    const bool make = !kUndo && L == a.len;
+#pragma unroll
+    for (int m = 0; m < (1 << kLog); ++m) {
+        const size_t j = base + i + (size_t)m * step;
+        if (!make)
+            x[m] = buf[j];
+        else if (!a.chirp)
+            x[m] = make_double2(profile_value(a.prof, off, (int)j), 0.0);
+        else
+            x[m] = which ? chirp_filter(a, (int)j) : chirped(a, off, (int)j);
     }
-    const int m = j < n ? j : (j > M - n ? M - j : -1);
-    if (m >= 0) {
-        const double2 c = chirp(m, n);
-        B[j] = make_double2(c.x, -c.y);
-    } else {
-        B[j] = make_double2(0.0, 0.0);
+    const double unit = 1.0 / step;
+    stages<kLog, kUndo>(x, i, step, [&](int r, int l) { return twiddle(r, unit / (1 << l)); });
+    const bool last = kUndo && L == a.len;
+    const double inv = 1.0 / a.len;
+#pragma unroll
+    for (int m = 0; m < (1 << kLog); ++m) {
+        const size_t j = base + i + (size_t)m * step;
+        if (last)
+            put_spectrum(a, (uint32_t)j, make_double2(x[m].x * inv, x[m].y * inv), a.norm);
+        else
+            buf[j] = x[m];
     }
 }
 
-__global__ void cmul_kernel(double2 *A, const double2 *B, int32_t M)
+// blockIdx.y: axis, blockIdx.z: operand of a chirped axis.  Pass number `pass`
+// (counted from the whole transform down) of each axis that has one.
+template <bool kUndo>
+__global__ __launch_bounds__(kWideThreads) void fft_wide_kernel(Axes axes, int pass)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= M) return;
-    const double2 a = A[j], b = B[j];
-    A[j] = make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    const Axis &a = axes.ax[blockIdx.y];
+    if (blockIdx.z && (!a.chirp || kUndo)) return;
+    if (kUndo && !a.chirp) return;
+    const int left = a.log2len - kTileLog - pass * kWideLog;  // wide stages from this pass on
+    if (left <= 0) return;
+    const int log = left < kWideLog ? left : kWideLog;
+    const int32_t L = a.len >> (pass * kWideLog);
+    if ((int)blockIdx.x * kWideThreads >= (a.len >> log)) return;  // whole workgroups
+    const int t = blockIdx.x * kWideThreads + threadIdx.x;
+    __shared__ int64_t off[kUndo ? 1 : kMaxBlocks + 1], lds[32];
+    if (!kUndo && pass == 0 && blockIdx.z == 0) profile_offsets(a.prof, off, lds);
+    switch (log) {
+    case 1: wide_pass<1, kUndo>(a, off, blockIdx.z, t, L); break;
+    case 2: wide_pass<2, kUndo>(a, off, blockIdx.z, t, L); break;
+    case 3: wide_pass<3, kUndo>(a, off, blockIdx.z, t, L); break;
+    default: wide_pass<4, kUndo>(a, off, blockIdx.z, t, L); break;
+    }
 }
 
-// X_k = c_k conv_k, conv = (the undone transform) / M, natural order.
-__global__ void unchirp_kernel(const double2 *conv, int32_t n, int32_t M, double2 *x)
+// value i of a tile, one value of padding per eight: eight consecutive values per
+// lane, and values a power of two apart, spread over the banks
+__device__ __forceinline__ int slot(int i) { return i + (i >> 3); }
+
+// The stages of a tile of T = 2^logT values in LDS, up to three at a time.  tw[j] =
+// e^{-2 pi i j / T}, j < T / 2, so e^{-i pi r / h} = tw[r T / (2 h)].
+template <int kLog, bool kUndo>
+__device__ __forceinline__ void tile_pass(double2 *tile, const double2 *tw, int logT, int logL)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const double2 c = chirp(k, n), v = conv[k];
-    const double inv = 1.0 / M;
-    x[k] = make_double2((v.x * c.x - v.y * c.y) * inv, (v.x * c.y + v.y * c.x) * inv);
+    const int T = 1 << logT, logstep = logL - kLog;
+    for (int t = threadIdx.x; t < (T >> kLog); t += kFftThreads) {
+        const int i = t & ((1 << logstep) - 1);
+        const int base = (t - i) << kLog;
+        double2 x[1 << kLog];
+#pragma unroll
+        for (int m = 0; m < (1 << kLog); ++m) x[m] = tile[slot(base + i + (m << logstep))];
+        stages<kLog, kUndo>(x, i, 1 << logstep, [&](int r, int l) { return tw[r << (logT - 1 - logstep - l)]; });
+#pragma unroll
+        for (int m = 0; m < (1 << kLog); ++m) tile[slot(base + i + (m << logstep))] = x[m];
+    }
+    __syncthreads();
 }
 
-// S(n) = |Z(n)|^2 / (Lx Ly) for n = 0 .. len/2 from the transform, in
-// bit-reversed order (log2len > 0) or natural order (log2len = 0); S(0) = 0
-// exactly (the mean is subtracted by definition).
-__global__ void spectrum_kernel(const double2 *z, int32_t len, int32_t log2len, double norm,
-                                double *S)
+template <bool kUndo>
+__device__ __forceinline__ void tile_stages(double2 *tile, const double2 *tw, int logT)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k > (len >> 1)) return;
-    const uint32_t j = log2len > 0 ? __brev((uint32_t)k) >> (32 - log2len) : (uint32_t)k;
-    const double2 v = z[j];
-    S[k] = k == 0 ? 0.0 : (v.x * v.x + v.y * v.y) * norm;
+    const int rest = logT % 3;
+    if (!kUndo) {
+        int logL = logT;
+        for (; logL >= 3; logL -= 3) tile_pass<3, false>(tile, tw, logT, logL);
+        if (rest == 2) tile_pass<2, false>(tile, tw, logT, 2);
+        if (rest == 1) tile_pass<1, false>(tile, tw, logT, 1);
+    } else {
+        if (rest == 2) tile_pass<2, true>(tile, tw, logT, 2);
+        if (rest == 1) tile_pass<1, true>(tile, tw, logT, 1);
+        for (int logL = rest + 3; logL <= logT; logL += 3) tile_pass<3, true>(tile, tw, logT, logL);
+    }
 }
 
-int log2_exact(int32_t n)
+// One tile (blockIdx.x) of axis blockIdx.y.  A plain axis: the remaining forward
+// stages and the spectrum.  A chirped one: the remaining stages of both operands, their
+// product, and the product's first undone stages (all of them, and the spectrum,
+// if the transform is one tile).
+__global__ __launch_bounds__(kFftThreads) void fft_tile_kernel(Axes axes)
+{
+    __shared__ double2 tile[kTile + kTile / 8], tw[kTile / 2];
+    __shared__ int64_t off[kTile / kProfThreads + 1], lds[32];
+    const Axis &a = axes.ax[blockIdx.y];
+    const int logT = a.log2len < kTileLog ? a.log2len : kTileLog, T = 1 << logT;
+    if ((int)blockIdx.x >= (a.len >> logT)) return;
+    for (int j = threadIdx.x; j < (T >> 1); j += kFftThreads) tw[j] = twiddle(j, 2.0 / T);
+    const size_t base = (size_t)blockIdx.x << logT;
+    const bool whole = a.log2len <= kTileLog;  // no wide pass made the operands
+    if (whole) profile_offsets(a.prof, off, lds);
+    if (!a.chirp) {
+        for (int i = threadIdx.x; i < T; i += kFftThreads) 
+            tile[slot(i)] = whole ? make_double2(profile_value(a.prof, off, i), 0.0) : a.z[base + i];
+        __syncthreads();
+        tile_stages<false>(tile, tw, logT);
+        for (int i = threadIdx.x; i < T; i += kFftThreads)
+            put_spectrum(a, __brev((uint32_t)(base + i)) >> (32 - a.log2len), tile[slot(i)], a.norm);
+        return;
+    }
+    constexpr int kEach = kTile / kFftThreads;
+    double2 first[kEach];
+    for (int i = threadIdx.x; i < T; i += kFftThreads) tile[slot(i)] = whole ? chirped(a, off, i) : a.A[base + i];
+    __syncthreads();
+    tile_stages<false>(tile, tw, logT);
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) {
+        const int i = threadIdx.x + e * kFftThreads;
+        if (i < T) first[e] = tile[slot(i)];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < T; i += kFftThreads) tile[slot(i)] = whole ? chirp_filter(a, i) : a.B[base + i];
+    __syncthreads();
+    tile_stages<false>(tile, tw, logT);
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) {
+        const int i = threadIdx.x + e * kFftThreads;
+        if (i < T) tile[slot(i)] = cmul(first[e], tile[slot(i)]);
+    }
+    __syncthreads();
+    tile_stages<true>(tile, tw, logT);
+    const double inv = 1.0 / a.len;
+    for (int i = threadIdx.x; i < T; i += kFftThreads) {
+        const double2 x = tile[slot(i)];
+        if (whole)
+            put_spectrum(a, (uint32_t)i, make_double2(x.x * inv, x.y * inv), a.norm);
+        else
+            a.A[base + i] = x;
+    }
+}
+
+int log2_exact(int64_t n)
 {
     int l = 0;
     while ((int64_t(1) << l) < n) ++l;
@@ -354,143 +593,153 @@ int64_t conv_len(int64_t n)
     return M;
 }
 
-// Forward transform of n = 2^k values in place, output bit-reversed.
-hipError_t launch_fft(double2 *z, int32_t n, hipStream_t st)
+// The transforms and spectra of the axes in [first, first + count).
+hipError_t launch_transforms(const Axes &axes, int count, hipStream_t st)
 {
-    const int T = n < kTile ? n : kTile;
-    for (int32_t h = n >> 1; 2 * h > T; h >>= 1)
-        hipLaunchKernelGGL(fft_stage_kernel<false>, dim3((n / 2 + kFftThreads - 1) / kFftThreads),
-                           dim3(kFftThreads), 0, st, z, n, h);
-    hipLaunchKernelGGL(fft_tile_kernel<false>, dim3(n / T), dim3(kFftThreads), 0, st, z, T);
-    return hipGetLastError();
-}
-
-// launch_fft undone: bit-reversed spectrum in, n x the inverse DFT out.
-hipError_t launch_fft_undo(double2 *z, int32_t n, hipStream_t st)
-{
-    const int T = n < kTile ? n : kTile;
-    hipLaunchKernelGGL(fft_tile_kernel<true>, dim3(n / T), dim3(kFftThreads), 0, st, z, T);
-    for (int32_t h = T; h < n; h <<= 1)
-        hipLaunchKernelGGL(fft_stage_kernel<true>, dim3((n / 2 + kFftThreads - 1) / kFftThreads),
-                           dim3(kFftThreads), 0, st, z, n, h);
-    return hipGetLastError();
-}
-
-// The DFT of the n values of z, in place: bit-reversed when n is a power of
-// two (returns log2 n), natural order through Bluestein otherwise (returns 0);
-// A and B hold conv_len(n) values each.
-hipError_t transform(double2 *z, int32_t n, double2 *A, double2 *B, int *order, hipStream_t st)
-{
-    if (pow2(n)) {
-        *order = log2_exact(n);
-        return launch_fft(z, n, st);
+    int most = 0, undo = 0, z = 1;
+    int64_t tiles = 1;
+    for (int i = 0; i < count; ++i) {
+        const Axis &a = axes.ax[i];
+        const int wide = a.log2len > kTileLog ? (a.log2len - kTileLog + kWideLog - 1) / kWideLog : 0;
+        most = wide > most ? wide : most;
+        if (a.chirp) {
+            undo = wide > undo ? wide : undo;
+            z = 2;
+        }
+        const int64_t t = a.log2len > kTileLog ? a.len >> kTileLog : 1;
+        tiles = t > tiles ? t : tiles;
     }
-    *order = 0;
-    const int32_t M = (int32_t)conv_len(n);
-    hipLaunchKernelGGL(chirp_kernel, dim3((M + 255) / 256), dim3(256), 0, st, z, n, M, A, B);
-    hipError_t e = launch_fft(A, M, st);
-    if (e != hipSuccess) return e;
-    e = launch_fft(B, M, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cmul_kernel, dim3((M + 255) / 256), dim3(256), 0, st, A, B, M);
-    e = launch_fft_undo(A, M, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(unchirp_kernel, dim3((n + 255) / 256), dim3(256), 0, st, A, n, M, z);
+    auto wide_blocks = [&](int pass) {
+        int64_t b = 1;
+        for (int i = 0; i < count; ++i) {
+            const int left = axes.ax[i].log2len - kTileLog - pass * kWideLog;
+            if (left <= 0) continue;
+            const int64_t n = (axes.ax[i].len >> (left < kWideLog ? left : kWideLog)) / kWideThreads;
+            b = n > b ? n : b;
+        }
+        return (unsigned)b;
+    };
+    for (int pass = 0; pass < most; ++pass)
+        hipLaunchKernelGGL(fft_wide_kernel<false>, dim3(wide_blocks(pass), count, z), dim3(kWideThreads), 0, st, axes,
+                           pass);
+    hipLaunchKernelGGL(fft_tile_kernel, dim3((unsigned)tiles, count), dim3(kFftThreads), 0, st, axes);
+    for (int pass = undo - 1; pass >= 0; --pass)
+        hipLaunchKernelGGL(fft_wide_kernel<true>, dim3(wide_blocks(pass), count, 1), dim3(kWideThreads), 0, st, axes,
+                           pass);
     return hipGetLastError();
 }
 
-}  // namespace
+int32_t blocks_of(int64_t n) { return (int32_t)((n + kProfThreads - 1) / kProfThreads); }
 
-namespace {
-
-// Scratch layout for column-count chunks of R rows (R a multiple of 16).
-PsdPlan plan_with_rows(int64_t Lx, int64_t Ly, int64_t R)
+// Scratch layout for R rows per workgroup of the plane pass (a multiple of
+// kPlaneWaves * kGroupRows).  The transforms take the place of the plane pass's
+// parts, which are added up by then.  together: both axes'
+// Bluestein buffers at once.
+PsdPlan plan_with_rows(int64_t Lx, int64_t Ly, int64_t R, bool together)
 {
     PsdPlan p{};
     p.R = (int32_t)R;
     p.nch = (int32_t)((Ly + R - 1) / R);
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-    p.off_cnt = al((size_t)p.nch * Lx * 4);
-    p.off_zx = p.off_cnt + al((size_t)Lx * 4);
-    p.off_zy = p.off_zx + al((size_t)Lx * 16);
-    p.off_spec = p.off_zy + al((size_t)Ly * 16);
-    p.off_blk = p.off_spec + al((size_t)(Lx / 2 + 1 + Ly / 2 + 1) * 8);
-    const size_t nbx = (Lx + kProfThreads - 1) / kProfThreads, nby = (Ly + kProfThreads - 1) / kProfThreads;
-    p.off_conv = p.off_blk + al((2 * (nbx + nby) + 4) * 8);
-    int64_t M = 0;  // Bluestein buffers, shared by the two sides in turn
-    if (!pow2(Lx)) M = conv_len(Lx);
-    if (!pow2(Ly) && conv_len(Ly) > M) M = conv_len(Ly);
-    p.conv_len = M;
-    p.bytes = p.off_conv + 2 * al((size_t)M * 16);
+    const size_t strips = (size_t)((Lx + kStripCols - 1) / kStripCols);
+    p.off_rowpart = al((size_t)p.nch * Lx * 4);
+    const size_t parts = p.off_rowpart + al(strips * (size_t)Ly * 8);
+    p.off_zx = 0;
+    p.off_zy = pow2(Lx) ? al((size_t)Lx * 16) : 0;
+    p.off_conv = p.off_zy + (pow2(Ly) ? al((size_t)Ly * 16) : 0);
+    const size_t Mx = pow2(Lx) ? 0 : (size_t)conv_len(Lx), My = pow2(Ly) ? 0 : (size_t)conv_len(Ly);
+    p.together = together || Mx == 0 || My == 0;
+    const size_t conv = p.together ? Mx + My : (Mx > My ? Mx : My);
+    const size_t work = p.off_conv + al(2 * conv * 16);
+    p.off_spec = parts > work ? parts : work;
+    p.off_prefix = p.off_spec + al((size_t)(Lx / 2 + 1 + Ly / 2 + 1) * 8);
+    p.off_blk = p.off_prefix + al((size_t)Lx * 4);
+    p.bytes = p.off_blk + al((2 * ((size_t)blocks_of(Lx) + blocks_of(Ly))) * 8);
     return p;
 }
+
+constexpr int64_t kRowStep = kPlaneWaves * kGroupRows;
+constexpr int64_t kMaxRows = (int64_t)kPlaneWaves * kMaxWaveRows;
 
 }  // namespace
 
-PsdPlan psd_plan(int64_t Lx, int64_t Ly)
-{
-    const int64_t W = Lx / 32;
-    const int64_t want = (kTargetThreads + W - 1) / W;  // chunks for ~2^18 threads
-    int64_t R = (Ly + want - 1) / want;
-    R = (R + 15) / 16 * 16;
-    return plan_with_rows(Lx, Ly, R);
-}
-
 PsdPlan psd_plan_capped(int64_t Lx, int64_t Ly, size_t max_bytes)
 {
-    PsdPlan p = psd_plan(Lx, Ly);
-    // fewer, taller chunks until the partial counts fit; a chunk's count of
-    // one column must stay below 2^20 (16-bit lanes of sixteens)
-    int64_t R = p.R;
-    while (p.bytes > max_bytes && R < Ly && 2 * R < (int64_t(1) << 20)) {
-        R *= 2;
-        p = plan_with_rows(Lx, Ly, R);
+    // enough workgroups to fill the device, then fewer and taller ones until the
+    // parts fit the bytes; both axes' transforms at once if they fit too
+    const int64_t strips = (Lx + kStripCols - 1) / kStripCols;
+    const int64_t chunks = (kPlaneTarget + strips - 1) / strips;
+    int64_t R = ((Ly + chunks - 1) / chunks + kRowStep - 1) / kRowStep * kRowStep;
+    if (R > kMaxRows) R = kMaxRows;
+    for (;; R = 2 * R < kMaxRows ? 2 * R : kMaxRows) {
+        for (int together = 1; together >= 0; --together) {
+            const PsdPlan p = plan_with_rows(Lx, Ly, R, together != 0);
+            if (p.bytes <= max_bytes) return p;
+            if (!together && (R >= Ly || R >= kMaxRows)) return p;  // the caller checks .bytes
+        }
     }
-    return p;
 }
 
-hipError_t launch_psd(const LatticeView &v, const PsdPlan &p, const int64_t *rows, void *scratch,
-                      hipStream_t st)
+// Within min(32 MiB, Lx Ly / 4) + 40 max(Lx, Ly) bytes, plus 128 max(Lx, Ly) when a
+// side is not a power of two (and the pieces' alignment).
+PsdPlan psd_plan(int64_t Lx, int64_t Ly)
+{
+    const size_t n = (size_t)Lx * Ly, most = (size_t)(Lx > Ly ? Lx : Ly);
+    const size_t parts = n / 4 < (size_t(32) << 20) ? n / 4 : size_t(32) << 20;
+    return psd_plan_capped(Lx, Ly, parts + 40 * most + (pow2(Lx) && pow2(Ly) ? 0 : 128 * most) + 2048);
+}
+
+hipError_t launch_psd(const LatticeView &v, const PsdPlan &p, int64_t *rows, void *scratch, hipStream_t st)
 {
     char *base = static_cast<char *>(scratch);
     int32_t *partial = reinterpret_cast<int32_t *>(base);
-    int32_t *cnt = reinterpret_cast<int32_t *>(base + p.off_cnt);
-    double2 *zx = reinterpret_cast<double2 *>(base + p.off_zx);
-    double2 *zy = reinterpret_cast<double2 *>(base + p.off_zy);
-    double *spec = reinterpret_cast<double *>(base + p.off_spec);
+    int2 *rowpart = reinterpret_cast<int2 *>(base + p.off_rowpart);
+    const int strips = (v.Lx + kStripCols - 1) / kStripCols;
+    if ((v.W & 3) == 0)
+        hipLaunchKernelGGL(plane_kernel<true>, dim3(strips, p.nch), dim3(kPlaneThreads), 0, st, v, p.R, partial,
+                           rowpart);
+    else
+        hipLaunchKernelGGL(plane_kernel<false>, dim3(strips, p.nch), dim3(kPlaneThreads), 0, st, v, p.R, partial,
+                           rowpart);
 
-    const int64_t nthr = (int64_t)v.W * p.nch;
-    hipLaunchKernelGGL(colcount_kernel, dim3((unsigned)((nthr + kCountThreads - 1) / kCountThreads)),
-                       dim3(kCountThreads), 0, st, v.planes, v.Ly, v.W, p.R, p.nch, partial);
-    hipLaunchKernelGGL(colsum_kernel, dim3((v.Lx + 255) / 256), dim3(256), 0, st, partial, p.nch,
-                       v.Lx, cnt);
-    const int32_t nbx = (v.Lx + kProfThreads - 1) / kProfThreads;
-    const int32_t nby = (v.Ly + kProfThreads - 1) / kProfThreads;
-    int64_t *bx = reinterpret_cast<int64_t *>(base + p.off_blk);
-    int64_t *by = bx + 2 * (size_t)nbx + 2;
-    hipLaunchKernelGGL(profile_sums_kernel<false>, dim3(nbx), dim3(kProfThreads), 0, st, cnt, rows,
-                       v.Lx, v.Ly, v.ox, bx);
-    hipLaunchKernelGGL(profile_sums_kernel<true>, dim3(nby), dim3(kProfThreads), 0, st, cnt, rows,
-                       v.Lx, v.Ly, v.ox, by);
-    hipLaunchKernelGGL(profile_offsets_kernel, dim3(1), dim3(kScanThreads), 0, st, bx, nbx, v.Lx);
-    hipLaunchKernelGGL(profile_offsets_kernel, dim3(1), dim3(kScanThreads), 0, st, by, nby, v.Ly);
-    hipLaunchKernelGGL(profile_write_kernel<false>, dim3(nbx), dim3(kProfThreads), 0, st, cnt, rows,
-                       v.Lx, v.Ly, v.ox, bx, nbx, zx);
-    hipLaunchKernelGGL(profile_write_kernel<true>, dim3(nby), dim3(kProfThreads), 0, st, cnt, rows,
-                       v.Lx, v.Ly, v.ox, by, nby, zy);
-    double2 *A = reinterpret_cast<double2 *>(base + p.off_conv);
-    double2 *B = reinterpret_cast<double2 *>(base + p.off_conv + (p.bytes - p.off_conv) / 2);
-    int ox_order = 0, oy_order = 0;
-    hipError_t e = transform(zx, v.Lx, A, B, &ox_order, st);
+    Profiles pr{};
+    pr.v = v;
+    pr.partial = partial;
+    pr.rowpart = rowpart;
+    pr.nch = p.nch;
+    pr.prefix[0] = reinterpret_cast<int32_t *>(base + p.off_prefix);
+    pr.prefix[1] = reinterpret_cast<int32_t *>(rows + v.Ly);
+    pr.extra = rows;
+    pr.nblk[0] = blocks_of(v.Lx);
+    pr.nblk[1] = blocks_of(v.Ly);
+    pr.blk[0] = reinterpret_cast<int64_t *>(base + p.off_blk);
+    pr.blk[1] = pr.blk[0] + 2 * (size_t)pr.nblk[0];
+    hipLaunchKernelGGL(profile_steps_kernel, dim3((unsigned)(pr.nblk[0] + pr.nblk[1])), dim3(kProfThreads), 0, st, pr);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = transform(zy, v.Ly, A, B, &oy_order, st);
+
+    Axes axes{};
+    double2 *conv = reinterpret_cast<double2 *>(base + p.off_conv);
+    double *spec = reinterpret_cast<double *>(base + p.off_spec);
+    for (int i = 0; i < 2; ++i) {
+        Axis &a = axes.ax[i];
+        a.n = i ? v.Ly : v.Lx;
+        a.chirp = !pow2(a.n);
+        a.len = a.chirp ? (int32_t)conv_len(a.n) : a.n;
+        a.log2len = log2_exact(a.len);
+        a.prof = Profile{pr.prefix[i], i ? pr.extra : nullptr, pr.blk[i], i ? v.Lx : 1, a.n, pr.nblk[i]};
+        a.z = reinterpret_cast<double2 *>(base + (i ? p.off_zy : p.off_zx));
+        a.A = conv;
+        a.B = conv + a.len;
+        if (p.together && a.chirp) conv += 2 * (size_t)a.len;
+        a.S = i ? spec + v.Lx / 2 + 1 : spec;
+        a.norm = 1.0 / ((double)v.Lx * (double)v.Ly);
+    }
+    if (p.together) return launch_transforms(axes, 2, st);
+    e = launch_transforms(axes, 1, st);
     if (e != hipSuccess) return e;
-    const double norm = 1.0 / ((double)v.Lx * (double)v.Ly);
-    hipLaunchKernelGGL(spectrum_kernel, dim3((v.Lx / 2 + 256) / 256), dim3(256), 0, st, zx, v.Lx,
-                       ox_order, norm, spec);
-    hipLaunchKernelGGL(spectrum_kernel, dim3((v.Ly / 2 + 256) / 256), dim3(256), 0, st, zy, v.Ly,
-                       oy_order, norm, spec + v.Lx / 2 + 1);
-    return hipGetLastError();
+    axes.ax[0] = axes.ax[1];
+    return launch_transforms(axes, 1, st);
 }
 
 }  // namespace okpz

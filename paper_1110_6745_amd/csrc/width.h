@@ -13,8 +13,5 @@ hipError_t launch_width(const LatticeView &v, int64_t *rows, const int64_t *h0, 
                         hipStream_t st);
 
 size_t width_scratch_words(int64_t Ly);
-// The per-row sums of the spectrum, in rows[0 .. 3 Ly): sum of P, sum of P^2,
-// sigma_y bit at physical column 0.
-hipError_t launch_width_rows(const LatticeView &v, int64_t *rows, hipStream_t st);
 
 }  // namespace okpz

@@ -273,18 +273,6 @@ __global__ __launch_bounds__(kTotalThreads) void width_total_kernel(const int64_
     }
 }
 
-// One wavefront per row: rows[y] = sum_x P, rows[Ly + y] = sum_x P^2, rows[2 Ly + y] =
-// the sigma_y bit at physical column 0 (for the spectrum).
-__global__ __launch_bounds__(kRowThreads) void width_rows_kernel(LatticeView v, int64_t *rows)
-{
-    __shared__ uint32_t lut[256];
-    core::width_lut_build(lut);
-    __syncthreads();
-    const int y = blockIdx.x * kWaves + (threadIdx.x >> 6);
-    if (y >= v.Ly) return;
-    core::width_row(v, y, threadIdx.x & 63, lut, rows);
-}
-
 // Rows per wavefront: enough workgroups to fill the device (eight per CU), then
 // longer runs, so that a workgroup's copy of the table and its record are shared by
 // more rows.
@@ -292,14 +280,9 @@ int rows_per_wave(int64_t Ly) { return (int)((Ly + kWaves * 2048 - 1) / (kWaves 
 
 }  // namespace
 
-// the spectrum's rows; the records (at most one per kWaves rows) use their place
+// the batch kernel's and the spectrum's rows; the records (at most one per kWaves
+// rows) use their place
 size_t width_scratch_words(int64_t Ly) { return 3 * (size_t)Ly + 4 * (size_t)((Ly + 255) / 256) + 4; }
-
-hipError_t launch_width_rows(const LatticeView &v, int64_t *rows, hipStream_t st)
-{
-    hipLaunchKernelGGL(width_rows_kernel, dim3((v.Ly + kWaves - 1) / kWaves), dim3(kRowThreads), 0, st, v, rows);
-    return hipGetLastError();
-}
 
 hipError_t launch_width(const LatticeView &v, int64_t *rows, const int64_t *h0, int64_t *out, int64_t t,
                         hipStream_t st)

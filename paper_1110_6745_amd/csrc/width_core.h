@@ -1,13 +1,12 @@
 // Device side of the exact squared width (Sec. I height reconstruction,
-// Eq. (Wdef)); shared by the per-lattice width kernels and the persistent
-// batch kernel.
+// Eq. (Wdef)) inside the persistent batch kernel, and workgroup scans and sums shared
+// with the per-lattice width and spectrum kernels.
 //
 // h(x,y) = H0 + G(y) + P_y(x), with G(y) = sum_{k<y} sigma_y(0,k) and
 // P_y(x) = sum_{l<x} sigma_x(l,y).  width_row: one wavefront reads row y's
-// words once, in stored order with aligned 16-byte loads; each lane takes
-// four consecutive words, sums them chunk by chunk through a 256-entry table
-// of 8-site partial sums, a wavefront prefix scan of the segments' height
-// changes gives every segment's starting height, and the row's rotation is
+// words once, in stored order, a word per lane; each lane sums its word chunk by
+// chunk through a 256-entry table of 8-site partial sums, a wavefront prefix scan of the
+// words' height changes gives every word's starting height, and the row's rotation is
 // undone in closed form at the end.  width_combine: one workgroup
 // scans the column-0 sigma_y bits to get G(y) and combines the rows into
 // 128-bit S1' = sum (h - H0) and S2' = sum (h - H0)^2.
@@ -42,14 +41,13 @@ __device__ __forceinline__ void width_lut_build(uint32_t *lut)
 // writes rows[y] = sum_x P, rows[Ly + y] = sum_x P^2, rows[2 Ly + y] = the
 // sigma_y bit at physical column 0.  lut: the chunk table in LDS.
 //
-// The row is read in stored order, kWpl words per lane per pass (four: one
-// aligned 16-byte load; one for narrow rows, with fewer registers).
+// The row is read in stored order, a word per lane and pass (few registers: a
+// 1024 x 1024 lattice's rows are 32 words, one pass).
 // With Q(c) the sigma_x prefix over stored columns c' < c and xs0 the stored
 // column of physical column 0, the full row sums to zero (a periodic row), so
 // P(x) = Q((xs0 + x) mod Lx) - Q(xs0) for every x; the physical sums follow
 // from the stored-order ones:
 //   sum P = sum Q - Lx Q(xs0),  sum P^2 = sum Q^2 - 2 Q(xs0) sum Q + Lx Q(xs0)^2.
-template <int kWpl = 4>
 __device__ __forceinline__ void width_row(const LatticeView &v, int y, int lane,
                                          const uint32_t *lut, int64_t *rows)
 {
@@ -57,28 +55,15 @@ __device__ __forceinline__ void width_row(const LatticeView &v, int y, int lane,
     const int xs0 = (v.Lx - v.ox) % v.Lx;  // stored column of physical column 0
     const int wq = xs0 >> 5;
     const uint32_t bq = (uint32_t)(xs0 & 31);
-    const bool vec = (v.W & 3) == 0;  // rows are 16-byte aligned
 
     int64_t a1 = 0, a2 = 0, q0 = 0;
     int32_t carry = 0;
-    for (int base = 0; base < v.W; base += 64 * kWpl) {
-        const int k0 = base + lane * kWpl;
-        const int nw = max(0, min(kWpl, v.W - k0));  // words of this lane
-        uint32_t wd[kWpl];
-#pragma unroll
-        for (int t = 0; t < kWpl; ++t) wd[t] = 0u;
-        if (kWpl == 4 && vec && nw == kWpl) {
-            const uint4 q = *reinterpret_cast<const uint4 *>(row + k0);
-            wd[0] = q.x; wd[1] = q.y; wd[2] = q.z; wd[3] = q.w;
-        } else {
-#pragma unroll
-            for (int t = 0; t < kWpl; ++t)
-                if (t < nw) wd[t] = row[k0 + t];
-        }
-        // heights relative to the first site of the lane's segment; every
-        // pass but the last has four words in every lane (a uniform test)
+    for (int base = 0; base < v.W; base += 64) {
+        const int k = base + lane;
+        const uint32_t word = k < v.W ? row[k] : 0u;
+        // heights relative to the first site of the word
         int32_t B = 0, S1 = 0, S2 = 0;
-        auto chunks = [&](uint32_t word) {
+        if (k < v.W) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t e = lut[(word >> (8 * j)) & 255u];
@@ -87,37 +72,8 @@ __device__ __forceinline__ void width_row(const LatticeView &v, int y, int lane,
                 const int32_t d = (int32_t)(int8_t)(e >> 16);
                 const int32_t t1 = 8 * B + s1;
                 S1 += t1;
-                S2 += __mul24(B, t1 + s1) + s2;  // |B| <= 128: a 24-bit multiply
+                S2 += __mul24(B, t1 + s1) + s2;  // |B| <= 32: a 24-bit multiply
                 B += d;
-            }
-        };
-        if (base + 64 * kWpl <= v.W) {
-#pragma unroll
-            for (int t = 0; t < kWpl; ++t) chunks(wd[t]);
-        } else {
-#pragma unroll
-            for (int t = 0; t < kWpl; ++t)
-                if (t < nw) chunks(wd[t]);
-        }
-        // Q(xs0): only in the pass holding word wq (a uniform test), and there
-        // only in the lane holding it
-        int32_t qrel = 0;
-        bool hasq = false;
-        if (wq >= base && wq < base + 64 * kWpl) {
-            const int tq = wq - k0;
-            if (tq >= 0 && tq < kWpl) {
-                int32_t Bq = 0;
-                uint32_t word = wd[0];
-#pragma unroll
-                for (int t = 1; t < kWpl; ++t) {
-                    if (t <= tq) {
-                        Bq += 2 * (int32_t)__popc(wd[t - 1]) - 32;
-                        word = wd[t];
-                    }
-                }
-                const uint32_t below = bq ? (word & ((1u << bq) - 1u)) : 0u;
-                qrel = Bq + 2 * (int32_t)__popc(below) - (int32_t)bq;
-                hasq = true;
             }
         }
         int32_t incl = B;
@@ -126,11 +82,14 @@ __device__ __forceinline__ void width_row(const LatticeView &v, int y, int lane,
             const int32_t t = __shfl_up(incl, o, 64);
             if (lane >= o) incl += t;
         }
-        const int64_t b = carry + incl - B;  // Q at the segment's first site
-        const int64_t n = 32 * nw;
+        const int64_t b = carry + incl - B;  // Q at the word's first site
+        const int64_t n = k < v.W ? 32 : 0;
         a1 += n * b + S1;
         a2 += n * b * b + 2 * b * S1 + S2;
-        if (hasq) q0 = b + qrel;
+        if (k == wq) {  // Q(xs0), in the lane holding its word
+            const uint32_t below = bq ? (word & ((1u << bq) - 1u)) : 0u;
+            q0 = b + 2 * (int32_t)__popc(below) - (int32_t)bq;
+        }
         carry += __shfl(incl, 63, 64);
     }
 #pragma unroll
