@@ -12,14 +12,16 @@
 // exact width when a sampling time is reached, and reopens the job's claim
 // word for the next sweep.  No workgroup ever waits for a particular other
 // workgroup, so the launch needs no co-residency; a workgroup that finds no
-// open group sleeps briefly and rescans, and a global progress counter acts
+// open group pauses, longer each time, and rescans, and a global progress counter acts
 // as watchdog: if no group completes anywhere for a long time every
 // workgroup exits with an error flag instead of spinning forever.
 //
 // Memory ordering: lattice words written by one workgroup are read by the
 // next sweep's workgroups on any XCD.  Scans are relaxed loads; a successful
-// claim is followed by one agent-scope acquire, a completed group by one
-// acquire-release count, and a reopened job by one release.
+// claim is followed by one agent-scope acquire; a completed item's words are
+// stored through to memory and waited for before its count; the workgroup that
+// completes a sweep acquires, and releases with the reopened job.  A job that one
+// workgroup advances alone is stored normally and released when it is published.
 //
 // A job's trajectory is identical to the same job run alone through
 // okpz_sweep: the random decisions are keyed by (seed, sweep, block, step,
@@ -47,7 +49,7 @@ namespace batch {
 struct JobDesc {
     uint32_t *buf[2];
     int64_t *h0;
-    int64_t *rows;      // width scratch, 3 * Ly
+    int64_t *rows;      // width scratch of the per-lattice width launches (served large jobs)
     int64_t *samples;   // nsamp x 6: t, S1' lo, S1' hi, S2' lo, S2' hi, H0
     const int32_t *sample_t;
     int32_t nsamp;
@@ -135,8 +137,6 @@ __device__ __forceinline__ void run_group(const SweepLaunch &a, int b0, int G, u
 // the job's state for the new sweep has been written.
 __device__ void publish(const JobDesc &jd, const JobState &ns, Control *ctl, uint64_t *claim, int r)
 {
-    // one completed sweep: the watchdog's sign of life
-    __hip_atomic_fetch_add(&ctl->progress, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (ns.s >= jd.t_max) {
         __hip_atomic_store(&claim[r], ((uint64_t)ns.s << 32) | kClosed, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
@@ -153,10 +153,30 @@ __device__ void publish(const JobDesc &jd, const JobState &ns, Control *ctl, uin
 //     while its claims and completion counts are halved;
 //   kClaimSticky: a workgroup first tries the job of its previous claim
 //     (one fetch-and-add, no scan of the claim words).
-// Ensembles use both (10 % faster on the finite-size-scaling mix); serving
-// uses neither: its quanta end with the slowest job's chain of sweeps, which
-// fewer workgroups per sweep lengthen (p50 and p99 latency rose with them).
+// Both pay where workgroups are scarce, and lengthen the jobs' chains of sweeps
+// where they are not (claim_policy).  Serving uses neither: its quanta end with the
+// slowest job's chain of sweeps.
 constexpr int32_t kClaimPairs = 1, kClaimSticky = 2;
+
+// Policy of an ensemble by its items per sweep (all jobs) per workgroup.  Measured
+// on growth ensembles at 1024 threads x 512 workgroups, none / pairs / both: 64 jobs of
+// 1024^2 (2 items per workgroup) 21.8 / 27.9 / 29.2 ms, 256 jobs of 32^2 to 1024^2
+// (3 items) 106.7 / 104.7 / 106.8 ms, 512 of them (6) 200 / 174.7 / 171.8 ms.
+inline int32_t claim_policy(int64_t items, int64_t workgroups)
+{
+    if (2 * items < 5 * workgroups) return 0;
+    return items < 4 * workgroups ? kClaimPairs : kClaimPairs | kClaimSticky;
+}
+
+// Sweeps of a claim of a job whose sweep is one item: no other workgroup works on
+// it, so the claim's workgroup runs several sweeps in a row (and their widths)
+// before it publishes the job, without a claim, a hand-over and an acquire per sweep.
+// Those cost more than the sweep: 64 jobs of 32^2 to 128^2, 940 sweeps the longest,
+// took 52 ms with each, 14 ms with one in 32.  Short enough that the jobs' order
+// of priority still decides who gets the workgroups.
+constexpr int kChainSweeps = 32;
+
+constexpr int kMostPause = 128;  // units of 16 x 64 cycles
 __device__ __forceinline__ int items_per_claim(int32_t nitems, int32_t flags)
 {
     return (flags & kClaimPairs) && nitems >= 8 ? 2 : 1;
@@ -234,12 +254,14 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
     __shared__ __align__(16) uint8_t smem[okpz::core::kGroupLds];
     __shared__ int s_job;     // >= 0: work; -1: exit; -2: retry
     __shared__ uint64_t s_claim;
+    __shared__ int s_last;    // 1: the claim's last item completed the sweep
     __shared__ int s_width;   // 1: the job just reached a sampling time
-    __shared__ int64_t s_out[4];
+    __shared__ int s_more;    // 1: the next sweep follows at once
     const int tid = threadIdx.x;
     uint64_t idle = 0, seen = 0;
     const int32_t *nitems = sched, *order = sched + njobs;
     const uint64_t t_begin = budget ? (uint64_t)wall_clock64() : 0;
+    int pause = 1;  // units of 16 x 64 cycles (thread 0)
     int last = -1;  // job of the previous claim (wave 0, uniform)
 
     while (true) {
@@ -254,24 +276,32 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
                 } else if (r >= 0) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the job's state and lattice
                     idle = 0;
+                    pause = 1;
                 } else if (__hip_atomic_load(&ctl->finished, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_SYSTEM) >= njobs ||
                            __hip_atomic_load(&ctl->error, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_SYSTEM) != 0) {
                     r = -1;
                 } else {
-                    // nothing open: retry after a short sleep, unless no sweep
-                    // has completed anywhere for idle_limit probes
+                    // nothing open: retry after a pause that doubles up to about
+                    // 50 us, unless no sweep has completed anywhere for idle_limit
+                    // units of it.  Hundreds of workgroups scanning without a pause slow
+                    // the claims of those that work (128 jobs up to 896^2 at p = 0.95,
+                    // q = 0.05, 512 threads: 53 ms with pauses of one unit, 44 ms)
                     r = -2;
                     const uint64_t p = ld_rlx(&ctl->progress);
+                    idle += pause;
                     if (p != seen) {
                         seen = p;
                         idle = 0;
-                    } else if (++idle > idle_limit) {
+                    } else if (idle > idle_limit) {
                         __hip_atomic_store(&ctl->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         r = -1;
                     }
-                    if (r == -2) __builtin_amdgcn_s_sleep(16);
+                    if (r == -2) {
+                        for (int i = 0; i < pause; ++i) __builtin_amdgcn_s_sleep(16);
+                        pause = min(kMostPause, 2 * pause);
+                    }
                 }
                 s_job = r;
                 s_claim = w;
@@ -292,72 +322,90 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
 
         const int item = (int)(uint32_t)w;
         const JobDesc jd = jobs[r];
-        const JobState js = state[r];
-        const SweepLaunch a = make_launch(jd, js);
+        JobState js = state[r];
         const int n_items = min(items_per_claim(jd.nitems, claim_flags), jd.nitems - item);
         const int g_end = min(jd.ngroups, (item + n_items) * jd.chunk);
-        for (int gi = item * jd.chunk; gi < g_end; ++gi) {
-            const int b0 = gi * jd.G;
-            const int Gc = min(jd.G, jd.nbx * jd.nby - b0);
-            if (kGrowthOnly || jd.mode == core::kGrowth)
-                run_group<kThreads, core::kGrowth | kCells>(a, b0, Gc, smem);
-            else if constexpr (!kGrowthOnly) {
-                if (jd.mode == core::kFixed)
-                    run_group<kThreads, core::kFixed | kCells>(a, b0, Gc, smem);
-                else
-                    run_group<kThreads, core::kDraw | kCells>(a, b0, Gc, smem);
+        for (int left = jd.nitems == 1 ? kChainSweeps : 1;;) {
+            SweepLaunch a = make_launch(jd, js);
+            a.store_through = jd.nitems != 1;
+            __builtin_amdgcn_s_setprio(0);
+            for (int gi = item * jd.chunk; gi < g_end; ++gi) {
+                const int b0 = gi * jd.G;
+                const int Gc = min(jd.G, jd.nbx * jd.nby - b0);
+                if (kGrowthOnly || jd.mode == core::kGrowth)
+                    run_group<kThreads, core::kGrowth | kCells>(a, b0, Gc, smem);
+                else if constexpr (!kGrowthOnly) {
+                    if (jd.mode == core::kFixed)
+                        run_group<kThreads, core::kFixed | kCells>(a, b0, Gc, smem);
+                    else
+                        run_group<kThreads, core::kDraw | kCells>(a, b0, Gc, smem);
+                }
+                // this wavefront's stores have reached memory
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();  // the group's tile is reused by the next group
             }
-            __syncthreads();  // the group's tile is reused by the next group
-        }
-
-        if (tid == 0) {
-            s_width = 0;
-            // release these items' lattice words; the last item acquires
-            // all (the increments form one release sequence)
-            const uint32_t d = __hip_atomic_fetch_add(&state[r].done, (uint32_t)n_items,
-                                                      __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) +
-                               (uint32_t)n_items;
-            if (d == (uint32_t)jd.nitems) {  // last item of sweep s: advance the job
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                JobState ns = js;
-                ns.s = js.s + 1;
-                ns.ox = a.sx;
-                ns.cur = js.cur ^ 1;
-                ns.done = 0;
-                const bool sample = ns.next_sample < jd.nsamp && jd.sample_t[ns.next_sample] == ns.s;
-                state[r] = ns;
-                if (sample)
-                    s_width = 1;
-                else
-                    publish(jd, ns, ctl, claim, r);
+            // claims and hand-overs are on the jobs' critical paths: ahead of the
+            // steps of a co-resident workgroup (2 to 3 % of an ensemble)
+            __builtin_amdgcn_s_setprio(3);
+            if (tid == 0) {
+                bool last = true;
+                if (jd.nitems != 1) {
+                    // These items' lattice words and H0 were written with system-scope
+                    // stores and device-scope atomics, which every wavefront has waited
+                    // for before the barrier: nothing of them is dirty in a cache,
+                    // so the count needs no release, whose write-back of the
+                    // XCD's L2 per item took 3 to 6 % of an ensemble.  The last item
+                    // acquires all.
+                    const uint32_t d = __hip_atomic_fetch_add(&state[r].done, (uint32_t)n_items,
+                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+                                       (uint32_t)n_items;
+                    last = d == (uint32_t)jd.nitems;
+                    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                }
+                s_last = last;
+                if (last) {  // sweep s is done: the job advances
+                    // one completed sweep: the watchdog's sign of life
+                    __hip_atomic_fetch_add(&ctl->progress, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    s_width = js.next_sample < jd.nsamp && jd.sample_t[js.next_sample] == js.s + 1;
+                    s_more = left > 1 && js.s + 1 < jd.t_max &&
+                             !(budget && (uint64_t)wall_clock64() - t_begin > budget);
+                }
             }
+            __syncthreads();
+            if (!s_last) break;
+            js.s += 1;
+            js.ox = a.sx;
+            js.cur ^= 1;
+            js.done = 0;
+            const bool more = s_more;
+            if (s_width) {
+                const LatticeView v{js.cur ? jd.buf[1] : jd.buf[0], jd.Lx, jd.Ly, jd.W, js.ox};
+                uint32_t *lut = reinterpret_cast<uint32_t *>(smem + 20 * 1024);
+                core::width_lut_build(lut);
+                int64_t s1, s2;
+                core::width_workgroup(v, lut, reinterpret_cast<int64_t *>(smem), s1, s2);
+                if (tid == 0) {
+                    int64_t *o = jd.samples + 6 * (size_t)js.next_sample;
+                    o[0] = js.s;
+                    o[1] = s1;
+                    o[2] = s1 >> 63;
+                    o[3] = s2;
+                    o[4] = 0;
+                    o[5] = __hip_atomic_load(jd.h0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                js.next_sample += 1;
+            }
+            if (!more) {
+                if (tid == 0) {
+                    state[r] = js;
+                    publish(jd, js, ctl, claim, r);
+                }
+                break;
+            }
+            left -= 1;
+            __syncthreads();  // every thread has read the flags before they are rewritten
         }
         __syncthreads();
-        if (s_width) {
-            const JobState ns = state[r];
-            const LatticeView v{ns.cur ? jd.buf[1] : jd.buf[0], jd.Lx, jd.Ly, jd.W, ns.ox};
-            const int lane = tid & 63, wave = tid >> 6, nwave = kThreads / 64;
-            uint32_t *lut = reinterpret_cast<uint32_t *>(smem + 20 * 1024);
-            core::width_lut_build(lut);
-            __syncthreads();
-            for (int y = wave; y < jd.Ly; y += nwave) core::width_row(v, y, lane, lut, jd.rows);
-            __syncthreads();  // rows are read back by other waves of this workgroup (same CU)
-            core::width_combine(jd.rows, jd.Lx, jd.Ly, s_out, reinterpret_cast<int64_t *>(smem));
-            if (tid == 0) {
-                int64_t *o = jd.samples + 6 * (size_t)ns.next_sample;
-                o[0] = ns.s;
-                o[1] = s_out[0];
-                o[2] = s_out[1];
-                o[3] = s_out[2];
-                o[4] = s_out[3];
-                o[5] = __hip_atomic_load(jd.h0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                JobState n2 = ns;
-                n2.next_sample = ns.next_sample + 1;
-                state[r] = n2;
-                publish(jd, n2, ctl, claim, r);
-            }
-            __syncthreads();
-        }
     }
 }
 
@@ -525,17 +573,17 @@ struct Ring {
     int njobs;
     hipStream_t stream;
     int delayed_cells;  // 1: delayed thread-cell borders
+    int64_t items = 0;    // items of a sweep of every unfinished job
     uint64_t budget = 0;  // wall-clock ticks per launch (0: run to the end)
-    int32_t claim_flags = 0;  // kClaimPairs | kClaimSticky for ensembles
+    int32_t claim_flags = 0;  // claim_policy, for ensembles
     int growth_only = 0;  // 1: every job runs p = 1, q = 0
 };
 
 template <int kThreads, int kCells>
 hipError_t launch_ring(const Ring &R, int wgs)
 {
-    // about 2 s without any group completing anywhere (one probe: a scan of
-    // the claim words plus a sleep of 16 x 64 cycles)
-    const uint64_t idle_limit = 1ull << 19;
+    // about 2 s of pauses (units of 16 x 64 cycles) without any sweep completing anywhere
+    const uint64_t idle_limit = 1ull << 22;
     if (R.growth_only)
         hipLaunchKernelGGL((okpz::batch::batch_kernel<kThreads, kCells, true>), dim3(wgs), dim3(kThreads),
                            0, R.stream, R.desc, R.state, R.ctl, R.claim, R.sched, (int32_t)R.njobs,
@@ -559,6 +607,9 @@ hipError_t launch_cells(const Ring &R, int threads, int wgs)
 
 hipError_t launch_any(const Ring &R, int threads, int wgs)
 {
+    // No more workgroups than items that can be open at once: the others would only
+    // scan the claim words.
+    if (R.items > 0 && R.items < wgs) wgs = (int)R.items;
     if (R.delayed_cells) return launch_cells<okpz::core::kDelayedCells>(R, threads, wgs);
     return launch_cells<0>(R, threads, wgs);
 }
@@ -597,7 +648,8 @@ int run(okpz_batch *b, int threads, int wgs, float *ms, uint64_t budget = 0,
     BHIP(hipEventRecord(e0, b->stream));
     Ring R = ring_of(b);
     R.budget = budget;
-    R.claim_flags = okpz::batch::kClaimPairs | okpz::batch::kClaimSticky;
+    for (const auto &d : b->desc) R.items += d.nitems;
+    R.claim_flags = okpz::batch::claim_policy(R.items, wgs);
     hipError_t e = launch_any(R, threads, wgs);
     if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "batch launch: %s", hipGetErrorString(e));
     BHIP(hipEventRecord(e1, b->stream));
@@ -1476,6 +1528,7 @@ int okpz_serve_step(okpz_server *sv, int32_t *running, int32_t *waiting)
     std::vector<int32_t> sched(2 * (size_t)sv->max_slots, 0);
     std::vector<std::pair<int64_t, int64_t>> grid_jobs;  // (job, stop)
     int active = 0, finished = 0, n_small = 0;
+    int64_t items = 0;
     for (int i = 0; i < sv->max_slots; ++i) {
         std::memset(&desc[i], 0, sizeof(JobDesc));
         const int64_t k = sv->slot_job[i];
@@ -1498,6 +1551,7 @@ int okpz_serve_step(okpz_server *sv, int32_t *running, int32_t *waiting)
         desc[i].t_max = (int32_t)stop;
         claim[i] = (uint64_t)J.s << 32;
         sched[i] = J.desc.nitems;
+        items += J.desc.nitems;
         ++n_small;
     }
     {
@@ -1518,8 +1572,9 @@ int okpz_serve_step(okpz_server *sv, int32_t *running, int32_t *waiting)
     BHIP(hipEventCreate(&e1));
     BHIP(hipEventCreate(&eg));
     BHIP(hipEventRecord(e0, sv->stream));
-    const Ring R{sv->d_desc, sv->d_state, sv->d_ctl, sv->d_claim, sv->d_sched, sv->max_slots,
+    Ring R{sv->d_desc, sv->d_state, sv->d_ctl, sv->d_claim, sv->d_sched, sv->max_slots,
                  sv->stream, sv->cell_borders == OKPZ_CELLS_DELAYED ? 1 : 0};
+    R.items = items;
     if (n_small > 0) {
         Control ctl{};
         ctl.finished = finished;

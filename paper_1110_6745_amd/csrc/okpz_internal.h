@@ -75,6 +75,9 @@ struct SweepLaunch {
     int32_t col0, col_step, ncol;
     // compute units the launch has to itself (0: it shares the device)
     int32_t cus;
+    // persistent kernel only: other workgroups read the stored words next, so they
+    // go through to memory
+    int32_t store_through;
 };
 
 // Block shift of sweep s (host side; the kernel uses the same values).

@@ -224,8 +224,8 @@ __device__ __forceinline__ uint32_t origin_yx(uint32_t w, int odd) { return odd 
 // and a wave's 64 cells share a block (needs Bx By >= 4096).
 // smem: at least tile_bytes(Bx, By, G) bytes; opk: G * 36 words of LDS
 // (origins, then the blocks' placement when kFixedB = 0).
-// kStoreThrough: write the new lattice with system-scope stores, which go
-// through to memory instead of staying dirty in this XCD's L2 (the persistent
+// kStoreThrough: with a.store_through, write the new lattice with system-scope stores,
+// which go through to memory instead of staying dirty in this XCD's L2 (the persistent
 // kernel's hand-over to other XCDs then has little to write back).
 template <int kThreads, int kModeFull, int kFixedB, bool kStoreThrough = false, bool kLaneOrg = false>
 __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const int G,
@@ -730,7 +730,7 @@ __device__ __forceinline__ void sweep_group(SweepLaunch a, const int b0, const i
             return;
         }
         uint32_t *w0 = a.dst + (size_t)y * a.W + col, *w1 = w0 + plane;
-        if (kStoreThrough) {
+        if (kStoreThrough && a.store_through) {
             __hip_atomic_store(w0, ~bxw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(w1, ~byw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         } else {
