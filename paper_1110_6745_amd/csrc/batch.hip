@@ -33,6 +33,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -452,6 +454,15 @@ struct okpz_batch {
     std::vector<JobDesc> desc;
     double m;
     void *mem = nullptr;
+    // Every job's H0 and samples lie in one block, job r's at result_offs[r], which
+    // a completed run copies to `results` at once: 560 copies of a few hundred bytes,
+    // one for each job's samples and one for its H0, took 9 ms where the run took
+    // 105.  Blocks above kMostResults stay on the device, read job by job.
+    char *d_results = nullptr;
+    size_t results_size = 0;
+    std::vector<size_t> result_offs;
+    std::unique_ptr<char[]> results;
+    bool have_results = false;  // of the completed run (ran)
     void *io_mem = nullptr;  // staging of okpz_batch_get_lattice, allocated by the first one
     size_t io_size = 0;
     JobDesc *d_desc = nullptr;
@@ -493,6 +504,23 @@ int bfail(int code, const char *fmt, ...)
     } while (0)
 
 bool side_ok(int64_t L) { return L >= 32 && L <= 8192 && L % 32 == 0; }
+
+constexpr size_t kMostResults = size_t(64) << 20;  // host copy of a batch's results
+
+// A completed run: its results to the host.
+int finish(okpz_batch *b)
+{
+    b->have_results = false;
+    if (b->results_size <= kMostResults) {
+        if (!b->results) b->results.reset(new (std::nothrow) char[b->results_size]);
+        if (b->results) {
+            BHIP(hipMemcpy(b->results.get(), b->d_results, b->results_size, hipMemcpyDeviceToHost));
+            b->have_results = true;
+        }
+    }
+    b->ran = true;
+    return OKPZ_OK;
+}
 
 // Measurement times of Sec. III as the 32-bit sweep counts the job tables
 // hold (t_max < 2^31 is checked at submission).
@@ -690,6 +718,7 @@ int okpz_batch_create(okpz_batch **out, const okpz_job *jobs, int32_t n_jobs, do
     size_t total = al(n_jobs * sizeof(JobDesc)) + al(n_jobs * sizeof(JobState)) + al(sizeof(Control));
     uint64_t groups = 0;
     std::vector<size_t> offs(n_jobs);
+    b->result_offs.resize(n_jobs);
     for (int r = 0; r < n_jobs; ++r) {
         const okpz_job &j = jobs[r];
         okpz::Geometry g;
@@ -722,10 +751,13 @@ int okpz_batch_create(okpz_batch **out, const okpz_job *jobs, int32_t n_jobs, do
         groups += d.ngroups;
         offs[r] = total;
         const size_t lat = al(2 * (size_t)j.Ly * (size_t)(j.Lx / 32) * 4);
-        total += 2 * lat + al(8) + al(3 * (size_t)j.Ly * 8) + al(6 * 8 * (size_t)std::max(1, d.nsamp)) +
-                 al(4 * (size_t)std::max(1, d.nsamp));
+        total += 2 * lat + al(3 * (size_t)j.Ly * 8) + al(4 * (size_t)std::max(1, d.nsamp));
+        b->result_offs[r] = b->results_size;
+        b->results_size += al(8) + al(6 * 8 * (size_t)std::max(1, d.nsamp));
     }
     (void)groups;
+    const size_t roff = total;
+    total += b->results_size;
     const size_t qoff = total;
     total += al((size_t)n_jobs * 8) + al((size_t)n_jobs * 8);
     hipError_t e = hipMalloc(&b->mem, total);
@@ -738,6 +770,7 @@ int okpz_batch_create(okpz_batch **out, const okpz_job *jobs, int32_t n_jobs, do
     b->d_state = reinterpret_cast<JobState *>(base + al(n_jobs * sizeof(JobDesc)));
     b->d_ctl = reinterpret_cast<Control *>(base + al(n_jobs * sizeof(JobDesc)) +
                                            al(n_jobs * sizeof(JobState)));
+    b->d_results = base + roff;
     b->d_claim = reinterpret_cast<uint64_t *>(base + qoff);
     b->d_sched = reinterpret_cast<int32_t *>(base + qoff + al((size_t)n_jobs * 8));
     for (int r = 0; r < n_jobs; ++r) {
@@ -747,11 +780,10 @@ int okpz_batch_create(okpz_batch **out, const okpz_job *jobs, int32_t n_jobs, do
         const size_t lat = al(2 * (size_t)j.Ly * (size_t)(j.Lx / 32) * 4);
         d.buf[0] = reinterpret_cast<uint32_t *>(p);
         d.buf[1] = reinterpret_cast<uint32_t *>(p + lat);
-        d.h0 = reinterpret_cast<int64_t *>(p + 2 * lat);
-        d.rows = reinterpret_cast<int64_t *>(p + 2 * lat + al(8));
-        d.samples = reinterpret_cast<int64_t *>(p + 2 * lat + al(8) + al(3 * (size_t)j.Ly * 8));
-        int32_t *tt = reinterpret_cast<int32_t *>(p + 2 * lat + al(8) + al(3 * (size_t)j.Ly * 8) +
-                                                   al(6 * 8 * (size_t)std::max(1, d.nsamp)));
+        d.rows = reinterpret_cast<int64_t *>(p + 2 * lat);
+        d.h0 = reinterpret_cast<int64_t *>(b->d_results + b->result_offs[r]);
+        d.samples = d.h0 + al(8) / 8;
+        int32_t *tt = reinterpret_cast<int32_t *>(p + 2 * lat + al(3 * (size_t)j.Ly * 8));
         d.sample_t = tt;
         if (d.nsamp) {
             e = hipMemcpy(tt, b->times[r].data(), d.nsamp * 4, hipMemcpyHostToDevice);
@@ -824,8 +856,7 @@ int okpz_batch_run(okpz_batch *b)
     const int wgs = b->workgroups ? b->workgroups : 2 * b->cus;
     rc = run(b, b->threads, wgs, &b->last_ms);
     b->started = false;
-    if (rc == OKPZ_OK) b->ran = true;
-    return rc;
+    return rc == OKPZ_OK ? finish(b) : rc;
 }
 
 int okpz_batch_start(okpz_batch *b)
@@ -868,7 +899,7 @@ int okpz_batch_run_for(okpz_batch *b, double max_ms, int32_t *finished)
     if (finished) *finished = done;
     if (done == (int32_t)b->jobs.size()) {
         b->started = false;
-        b->ran = true;
+        return finish(b);
     }
     return OKPZ_OK;
 }
@@ -931,12 +962,19 @@ int okpz_batch_samples(okpz_batch *b, int32_t job, int64_t *t, int64_t *sum_h, i
     *count = n;
     if (!t && !sum_h && !sum_h2) return OKPZ_OK;
     if (cap < n) return bfail(OKPZ_EINVAL, "capacity %d < %d samples", cap, n);
-    std::vector<int64_t> raw(6 * (size_t)std::max(1, n));
-    BHIP(hipMemcpy(raw.data(), d.samples, 6 * 8 * (size_t)n, hipMemcpyDeviceToHost));
+    std::vector<int64_t> raw;
+    const int64_t *row;
+    if (b->have_results) {
+        row = reinterpret_cast<const int64_t *>(b->results.get() + b->result_offs[job]) + al(8) / 8;
+    } else {
+        raw.resize(6 * (size_t)std::max(1, n));
+        BHIP(hipMemcpy(raw.data(), d.samples, 6 * 8 * (size_t)n, hipMemcpyDeviceToHost));
+        row = raw.data();
+    }
     const __int128 N = (__int128)d.Lx * d.Ly;
     const __int128 lim = (__int128)1 << 63;
     for (int i = 0; i < n; ++i) {
-        const int64_t *o = &raw[6 * (size_t)i];
+        const int64_t *o = row + 6 * (size_t)i;
         const __int128 s1r = (__int128)(((unsigned __int128)(uint64_t)o[2] << 64) | (uint64_t)o[1]);
         const __int128 s2r = (__int128)(((unsigned __int128)(uint64_t)o[4] << 64) | (uint64_t)o[3]);
         const __int128 H0 = o[5];
@@ -1066,7 +1104,10 @@ int okpz_batch_h0(okpz_batch *b, int32_t job, int64_t *h0)
 {
     if (!b || !h0) return bfail(OKPZ_EINVAL, "null argument");
     if (job < 0 || job >= (int32_t)b->jobs.size()) return bfail(OKPZ_EINVAL, "job out of range");
-    BHIP(hipMemcpy(h0, b->desc[job].h0, 8, hipMemcpyDeviceToHost));
+    if (b->ran && b->have_results)
+        *h0 = *reinterpret_cast<const int64_t *>(b->results.get() + b->result_offs[job]);
+    else
+        BHIP(hipMemcpy(h0, b->desc[job].h0, 8, hipMemcpyDeviceToHost));
     return OKPZ_OK;
 }
 
