@@ -3,18 +3,20 @@
 // persistent launch (ensembles of independent runs, Sec. III and IV).
 //
 // Work item = (job, chunk of groups of blocks) of the job's current sweep
-// (one group per item for lattices up to 2048 x 2048; larger lattices hand
-// out at most 128 items per sweep).  Each job has a claim word (sweep << 32 |
+// (one group per item up to kItemsPerSweep groups, chunks of them above).  Each job has a claim word (sweep << 32 |
 // next item); a resident workgroup's first wavefront scans the claim words,
 // 64 jobs per load, and claims an item of a job with one fetch-and-add on
 // that job's word, so contention is spread over the jobs.  The workgroup that
-// completes the last item of a job's sweep advances the job (time, stored offset, lattice copy), measures the
-// exact width when a sampling time is reached, and reopens the job's claim
-// word for the next sweep.  No workgroup ever waits for a particular other
-// workgroup, so the launch needs no co-residency; a workgroup that finds no
-// open group pauses, longer each time, and rescans, and a global progress counter acts
-// as watchdog: if no group completes anywhere for a long time every
-// workgroup exits with an error flag instead of spinning forever.
+// completes the last item of a job's sweep advances the job (time, stored offset,
+// lattice copy), measures the exact width when a sampling time is reached, and
+// reopens the job's claim word for the next sweep.  Where there are workgroups
+// enough, those of a job's items stay with it from sweep to sweep and share the
+// width's rows (kClaimStay): 300 sweeps of two jobs of 2048^2 20.8 -> 8.3 ms.  A
+// workgroup waits only for items that running workgroups have claimed, so the
+// launch needs no co-residency; one that finds no open item pauses, longer each
+// time, and rescans, and a global progress counter acts as watchdog: if no sweep
+// completes anywhere for a long time every workgroup exits with an error flag
+// instead of spinning forever.
 //
 // Memory ordering: lattice words written by one workgroup are read by the
 // next sweep's workgroups on any XCD.  Scans are relaxed loads; a successful
@@ -68,7 +70,7 @@ struct JobState {
     int32_t ox;           // stored offset of the source copy
     int32_t cur;          // source copy
     int32_t next_sample;  // index of the next sampling time
-    uint32_t done;        // groups of sweep s completed
+    uint32_t done;        // items of sweep s completed (+ kStays for each whose workgroup stays)
     int32_t pad[3];
 };
 
@@ -83,8 +85,9 @@ struct Control {
 // kClosed in the low word.  A scan can see a word open that is exhausted or
 // closed by the time the wave's fetch-and-add lands; such late increments
 // are at most two (one claim) per workgroup per word value, so the low word
-// never carries into the sweep number (kClosed + 2 workgroups < 2^32).
-constexpr uint32_t kClosed = 0x80000000u;
+// never carries into the sweep number (kClosed + 2 workgroups < 2^32).  A job
+// advanced by a team (kClaimStay) holds kTeam: nothing to claim, but its members go on.
+constexpr uint32_t kClosed = 0x80000000u, kTeam = 0x40000000u;
 
 // Polled words (claim words, counters) are read and published at system
 // scope, which bypasses the per-XCD caches: a poller never spins on a stale
@@ -92,6 +95,33 @@ constexpr uint32_t kClosed = 0x80000000u;
 __device__ __forceinline__ uint64_t ld_rlx(uint64_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A job's descriptor, constant during a launch, in scalar registers.  (Plain loads
+// put it into a vector register per word, and the sweep's keys, thresholds and
+// addresses with it.)
+__device__ __forceinline__ JobDesc load_desc(const JobDesc *p)
+{
+    typedef const __attribute__((address_space(4))) uint32_t *Words;
+    constexpr int n = sizeof(JobDesc) / 4;
+    uint32_t w[n];
+    const Words q = (Words)(const uint32_t *)p;
+#pragma unroll
+    for (int i = 0; i < n; ++i) w[i] = q[i];
+    JobDesc d;
+    __builtin_memcpy(&d, w, sizeof d);
+    return d;
+}
+
+// A job's state, as its last sweep left it, in scalar registers.
+__device__ __forceinline__ JobState load_state(const JobState *p)
+{
+    JobState s = *p;
+    s.s = __builtin_amdgcn_readfirstlane(s.s);
+    s.ox = __builtin_amdgcn_readfirstlane(s.ox);
+    s.cur = __builtin_amdgcn_readfirstlane(s.cur);
+    s.next_sample = __builtin_amdgcn_readfirstlane(s.next_sample);
+    return s;
 }
 
 __device__ inline SweepLaunch make_launch(const JobDesc &jd, const JobState &js)
@@ -150,24 +180,42 @@ __device__ void publish(const JobDesc &jd, const JobState &ns, Control *ctl, uin
 }
 
 // Claim policy of a launch (flags):
-//   kClaimPairs: a workgroup takes two items of a job whose sweep has at
-//     least eight, so such a job still spreads over four or more workgroups
-//     while its claims and completion counts are halved;
 //   kClaimSticky: a workgroup first tries the job of its previous claim
 //     (one fetch-and-add, no scan of the claim words).
-// Both pay where workgroups are scarce, and lengthen the jobs' chains of sweeps
-// where they are not (claim_policy).  Serving uses neither: its quanta end with the
-// slowest job's chain of sweeps.
-constexpr int32_t kClaimPairs = 1, kClaimSticky = 2;
+//   kClaimStay: workgroups stay with a job.  One that has completed an item of a
+//     sweep with none left to claim waits for the sweep instead of looking for
+//     another job; if all the sweep's items have such a workgroup, they
+//     are a team and go on with the same items, sweep after sweep, with one count
+//     and one polled word each instead of a claim, a scan and an acquired state.
+//     A workgroup waits only for items that other running workgroups hold, so
+//     teams need no co-residency either.
+//   kClaimItems times k: a claim is k items of a job whose sweep has at least
+//     4 k, so such a job still spreads over four or more workgroups while its claims
+//     and counts are divided by k.
+constexpr int32_t kClaimSticky = 1, kClaimStay = 2, kClaimItems = 256;
+constexpr uint32_t kStays = 1u << 16;  // in JobState::done, above the items
 
-// Policy of an ensemble by its items per sweep (all jobs) per workgroup.  Measured
-// on growth ensembles at 1024 threads x 512 workgroups, none / pairs / both: 64 jobs of
-// 1024^2 (2 items per workgroup) 21.8 / 27.9 / 29.2 ms, 256 jobs of 32^2 to 1024^2
-// (3 items) 106.7 / 104.7 / 106.8 ms, 512 of them (6) 200 / 174.7 / 171.8 ms.
+__device__ __forceinline__ int items_per_claim(int32_t nitems, int32_t flags)
+{
+    return max(1, min(nitems / 4, flags / kClaimItems));
+}
+
+// Policy of an ensemble by its items per sweep (all jobs) per workgroup.  Up to
+// 1.5, nearly every item has a workgroup and the jobs' chains of sweeps bound the
+// run: teams.  Up to 2, the same in pairs.  Further up, the workgroups are
+// always busy: teams while a job's items are few of them, then pairs and sticky claims
+// for fewer atomics.  Measured in ms on 512 workgroups (items per workgroup: no
+// policy / stay / stay, pairs / sticky, pairs), growth at 1024 threads: 8 jobs of 1024^2 (0.25)
+// 10.1 / 7.2 / 12.8 / 15.1, 6 of 2048^2 (0.75) 17.4 / 9.4 / 17.6 / 25.0, 40 of 1024^2 (1.25)
+// 21.0 / 17.8 / 18.1 / 26.0, 64 (2) 20.6 / 23.6 / 18.6 / 26.5, 96 (3) 27.3 / 22.6 / 24.8 / 20.9,
+// 256 of 32^2 to 1024^2 (3) 101.8 / 98.5 / 101.3 / 102.6, 384 (4.5) 102.1 / 102.7 / 97.4 / 91.9,
+// 512 (6) 191.5 / 192.3 / 177.3 / 167.0; 128 up to 896^2 at p = 0.95, q = 0.05, 512 threads
+// (1.1) 41.5 / 29.7 / 56.4 / 61.2.
 inline int32_t claim_policy(int64_t items, int64_t workgroups)
 {
-    if (2 * items < 5 * workgroups) return 0;
-    return items < 4 * workgroups ? kClaimPairs : kClaimPairs | kClaimSticky;
+    if (2 * items <= 3 * workgroups) return kClaimStay + kClaimItems;
+    if (items <= 2 * workgroups) return kClaimStay + 2 * kClaimItems;
+    return 2 * items < 7 * workgroups ? kClaimStay + kClaimItems : kClaimSticky + 2 * kClaimItems;
 }
 
 // Sweeps of a claim of a job whose sweep is one item: no other workgroup works on
@@ -179,10 +227,6 @@ inline int32_t claim_policy(int64_t items, int64_t workgroups)
 constexpr int kChainSweeps = 32;
 
 constexpr int kMostPause = 128;  // units of 16 x 64 cycles
-__device__ __forceinline__ int items_per_claim(int32_t nitems, int32_t flags)
-{
-    return (flags & kClaimPairs) && nitems >= 8 ? 2 : 1;
-}
 
 // Wave 0 looks for an open item and claims items_per_claim of them (fewer
 // if the sweep has fewer left): first of job `prefer` (the job of the
@@ -236,6 +280,26 @@ __device__ int find_and_claim(uint64_t *claim, const int32_t *nitems, const int3
     return -1;
 }
 
+// Waits until sweep s of a job is complete: true if its team goes on.
+__device__ bool await_sweep(uint64_t *word, uint32_t s, Control *ctl, uint64_t idle_limit)
+{
+    uint64_t seen = 0, idle = 0;
+    for (uint32_t polls = 1;; ++polls) {
+        const uint64_t w = ld_rlx(word);
+        if ((uint32_t)(w >> 32) != s) return (uint32_t)w >= kTeam && (uint32_t)w < kClosed;
+        __builtin_amdgcn_s_sleep(4);
+        if (polls % 64 != 0) continue;
+        if (__hip_atomic_load(&ctl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0) return false;
+        const uint64_t p = ld_rlx(&ctl->progress);
+        idle = p == seen ? idle + 16 : 0;  // 64 pauses are 16 units
+        seen = p;
+        if (idle > idle_limit) {
+            __hip_atomic_store(&ctl->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        }
+    }
+}
+
 // kCells: 0 for dead thread-cell borders, core::kDelayedCells for delayed
 // ones (one kind per launch).  kGrowthOnly: every job runs p = 1, q = 0, so
 // only that acceptance mode's sweep bodies are compiled in (fewer registers:
@@ -257,8 +321,8 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
     __shared__ int s_job;     // >= 0: work; -1: exit; -2: retry
     __shared__ uint64_t s_claim;
     __shared__ int s_last;    // 1: the claim's last item completed the sweep
-    __shared__ int s_width;   // 1: the job just reached a sampling time
-    __shared__ int s_more;    // 1: the next sweep follows at once
+    __shared__ int s_stay;    // 1: the workgroup waits for the sweep
+    __shared__ int s_more;    // 1: the workgroup goes on with the next sweep at once
     const int tid = threadIdx.x;
     uint64_t idle = 0, seen = 0;
     const int32_t *nitems = sched, *order = sched + njobs;
@@ -323,11 +387,15 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
         // next claim)
 
         const int item = (int)(uint32_t)w;
-        const JobDesc jd = jobs[r];
-        JobState js = state[r];
+        const JobDesc jd = load_desc(jobs + r);
+        JobState js = load_state(state + r);
         const int n_items = min(items_per_claim(jd.nitems, claim_flags), jd.nitems - item);
         const int g_end = min(jd.ngroups, (item + n_items) * jd.chunk);
-        for (int left = jd.nitems == 1 ? kChainSweeps : 1;;) {
+        auto sample_time = [&] { return js.next_sample < jd.nsamp ? jd.sample_t[js.next_sample] : -1; };
+        int next_t = sample_time();  // loaded a sample ahead
+        bool team = false;
+        uint32_t target = 0;  // the count that completes the team's sweep
+        for (int left = kChainSweeps;;) {
             SweepLaunch a = make_launch(jd, js);
             a.store_through = jd.nitems != 1;
             __builtin_amdgcn_s_setprio(0);
@@ -350,7 +418,7 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
             // steps of a co-resident workgroup (2 to 3 % of an ensemble)
             __builtin_amdgcn_s_setprio(3);
             if (tid == 0) {
-                bool last = true;
+                bool last = true, full = true;
                 if (jd.nitems != 1) {
                     // These items' lattice words and H0 were written with system-scope
                     // stores and device-scope atomics, which every wavefront has waited
@@ -358,36 +426,42 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
                     // so the count needs no release, whose write-back of the
                     // XCD's L2 per item took 3 to 6 % of an ensemble.  The last item
                     // acquires all.
-                    const uint32_t d = __hip_atomic_fetch_add(&state[r].done, (uint32_t)n_items,
-                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
-                                       (uint32_t)n_items;
-                    last = d == (uint32_t)jd.nitems;
+                    const bool stay = team || ((claim_flags & kClaimStay) &&
+                                               (uint32_t)ld_rlx(&claim[r]) >= (uint32_t)jd.nitems);
+                    const uint32_t add = (uint32_t)n_items * (!team && stay ? kStays + 1 : 1u);
+                    const uint32_t d = __hip_atomic_fetch_add(&state[r].done, add, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT) + add;
+                    last = team ? d == target : d % kStays == (uint32_t)jd.nitems;
+                    full = team || d / kStays == (uint32_t)jd.nitems;
                     if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                    s_stay = stay;
                 }
                 s_last = last;
                 if (last) {  // sweep s is done: the job advances
                     // one completed sweep: the watchdog's sign of life
                     __hip_atomic_fetch_add(&ctl->progress, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    s_width = js.next_sample < jd.nsamp && jd.sample_t[js.next_sample] == js.s + 1;
-                    s_more = left > 1 && js.s + 1 < jd.t_max &&
+                    s_more = (jd.nitems == 1 ? left > 1 : full) && js.s + 1 < jd.t_max &&
                              !(budget && (uint64_t)wall_clock64() - t_begin > budget);
                 }
             }
             __syncthreads();
-            if (!s_last) break;
+            const bool last = s_last;
+            if (!last && !s_stay) break;
             js.s += 1;
             js.ox = a.sx;
             js.cur ^= 1;
             js.done = 0;
-            const bool more = s_more;
-            if (s_width) {
-                const LatticeView v{js.cur ? jd.buf[1] : jd.buf[0], jd.Lx, jd.Ly, jd.W, js.ox};
-                uint32_t *lut = reinterpret_cast<uint32_t *>(smem + 20 * 1024);
+            const bool sample = next_t == js.s;
+            const LatticeView v{js.cur ? jd.buf[1] : jd.buf[0], jd.Lx, jd.Ly, jd.W, js.ox};
+            uint32_t *lut = reinterpret_cast<uint32_t *>(smem + 20 * 1024);
+            int64_t *part = reinterpret_cast<int64_t *>(smem);
+            int64_t *o = jd.samples + 6 * (size_t)js.next_sample;
+            int64_t s1, s2;
+            const bool alone = last && (!s_more || jd.nitems == 1);  // no team goes on
+            if (sample && alone) {
                 core::width_lut_build(lut);
-                int64_t s1, s2;
-                core::width_workgroup(v, lut, reinterpret_cast<int64_t *>(smem), s1, s2);
+                core::width_workgroup(v, lut, part, 0, jd.Ly, s1, s2);
                 if (tid == 0) {
-                    int64_t *o = jd.samples + 6 * (size_t)js.next_sample;
                     o[0] = js.s;
                     o[1] = s1;
                     o[2] = s1 >> 63;
@@ -395,16 +469,65 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
                     o[4] = 0;
                     o[5] = __hip_atomic_load(jd.h0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-                js.next_sample += 1;
             }
-            if (!more) {
+            if (sample) {
+                js.next_sample += 1;
+                next_t = sample_time();
+            }
+            if (alone) {
+                if (s_more) {
+                    left -= 1;
+                    __syncthreads();  // every thread has read the flags before they are rewritten
+                    continue;
+                }
                 if (tid == 0) {
                     state[r] = js;
                     publish(jd, js, ctl, claim, r);
                 }
                 break;
             }
-            left -= 1;
+            if (tid == 0) {
+                if (last) {
+                    if (sample) {  // the members add their rows' sums to a row of zeros
+                        const int64_t h0 = __hip_atomic_load(jd.h0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        for (int i = 0; i < 6; ++i)
+                            __hip_atomic_store(&o[i], i == 0 ? (int64_t)js.s : i == 5 ? h0 : 0, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_SYSTEM);
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    }
+                    if (!team) {  // the first of the team: its count starts at 0
+                        state[r] = js;
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    }
+                    __hip_atomic_store(&claim[r], (uint64_t)js.s << 32 | kTeam, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_SYSTEM);
+                } else {
+                    s_more = await_sweep(&claim[r], (uint32_t)(js.s - 1), ctl, idle_limit);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                }
+            }
+            __syncthreads();
+            if (!s_more) break;
+            target += (uint32_t)jd.nitems;
+            team = true;
+            if (sample) {
+                // Each member measures its share of the rows.  The next sweep
+                // writes the other copy, and the one after it starts when
+                // every member has counted the next: this copy stays as it is.
+                core::width_lut_build(lut);
+                core::width_workgroup(v, lut, part, jd.Ly * item / jd.nitems,
+                                      jd.Ly * (item + n_items) / jd.nitems, s1, s2);
+                if (tid == 0) {
+                    const uint64_t was = __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(o + 1), (uint64_t)s1,
+                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int64_t hi = (s1 >> 63) + (was + (uint64_t)s1 < was ? 1 : 0);  // 128-bit sum
+                    if (hi != 0)
+                        __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(o + 2), (uint64_t)hi, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(o + 3), (uint64_t)s2, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
             __syncthreads();  // every thread has read the flags before they are rewritten
         }
         __syncthreads();
@@ -603,7 +726,7 @@ struct Ring {
     int delayed_cells;  // 1: delayed thread-cell borders
     int64_t items = 0;    // items of a sweep of every unfinished job
     uint64_t budget = 0;  // wall-clock ticks per launch (0: run to the end)
-    int32_t claim_flags = 0;  // claim_policy, for ensembles
+    int32_t claim_flags = okpz::batch::kClaimItems;  // claim_policy, for ensembles
     int growth_only = 0;  // 1: every job runs p = 1, q = 0
 };
 
@@ -1628,6 +1751,7 @@ int okpz_serve_step(okpz_server *sv, int32_t *running, int32_t *waiting)
         BHIP(hipMemcpyAsync(sv->d_ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice, sv->stream));
         // beside plain sweeps, one persistent workgroup per CU leaves room for them
         const int wgs = sv->wgs ? sv->wgs : (grid_jobs.empty() ? 2 : 1) * sv->cus;
+        if (items <= wgs) R.claim_flags |= okpz::batch::kClaimStay;
         hipError_t e = launch_any(R, sv->threads, wgs);
         if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "serve launch: %s", hipGetErrorString(e));
     }

@@ -37,9 +37,9 @@ __device__ __forceinline__ void width_lut_build(uint32_t *lut)
     }
 }
 
-// Sums of h - H0 and its square over lattice view v, by the whole workgroup, in
-// thread 0's s1 and s2 (sides up to 8192: |h - H0| <= 2^14, so the sum of squares
-// over 2^26 sites stays below 2^54).  lut: the chunk table; part: LDS, four words
+// Sums of h - H0 and its square over rows [y_lo, y_hi) of lattice view v, by the whole
+// workgroup, in thread 0's s1 and s2 (sides up to 8192: |h - H0| <= 2^14, so the sum of
+// squares over 2^26 sites stays below 2^54).  lut: the chunk table; part: LDS, five words
 // per wavefront.  Starts and ends with a barrier.
 //
 // What bounds it: the latency of one workgroup's passes.  1024 x 1024: two rows per
@@ -47,7 +47,7 @@ __device__ __forceinline__ void width_lut_build(uint32_t *lut)
 // second pass over the rows' sums took about three times as long, a fifth of a
 // finite-size-scaling ensemble with a sample every ten to twenty sweeps.
 __device__ __forceinline__ void width_workgroup(const LatticeView &v, const uint32_t *lut, int64_t *part,
-                                                int64_t &s1, int64_t &s2)
+                                                int y_lo, int y_hi, int64_t &s1, int64_t &s2)
 {
     const int tid = threadIdx.x, lane = tid & 63, nwave = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -57,8 +57,11 @@ __device__ __forceinline__ void width_workgroup(const LatticeView &v, const uint
     // 2^ls lanes per row
     const int ls = v.W >= 64 ? 6 : v.W <= 1 ? 0 : 32 - __builtin_clz(v.W - 1);
     const int R = 64 >> ls, sub = lane >> ls, c = lane & ((1 << ls) - 1);
-    const int rpw = (v.Ly + nwave - 1) / nwave;
-    const int ya = min(v.Ly, wave * rpw), yb = min(v.Ly, ya + rpw);
+    const int rpw = (y_hi - y_lo + nwave - 1) / nwave;
+    const int ya = min(y_hi, y_lo + wave * rpw), yb = min(y_hi, ya + rpw);
+    int32_t g0 = 0;  // the wave's share of G(y_lo)
+    for (int y = tid; y < y_lo; y += (int)blockDim.x)
+        g0 += ((v.planes[(size_t)v.Ly * v.W + (size_t)y * v.W + wq] >> bq) & 1u) ? 1 : -1;
     __syncthreads();  // the table
 
     int64_t A = 0, B = 0;
@@ -112,16 +115,19 @@ __device__ __forceinline__ void width_workgroup(const LatticeView &v, const uint
     for (int o = 32; o > 0; o >>= 1) {
         A += __shfl_down(A, o, 64);
         B += __shfl_down(B, o, 64);
+        g0 += __shfl_down(g0, o, 64);
     }
     if (lane == 0) {
         part[4 * wave] = g;
         part[4 * wave + 1] = A;
         part[4 * wave + 2] = B;
         part[4 * wave + 3] = (int64_t)(yb - ya) * v.Lx;
+        part[4 * nwave + wave] = g0;
     }
     __syncthreads();
     if (tid == 0) {
         int64_t G = 0;
+        for (int w = 0; w < nwave; ++w) G += part[4 * nwave + w];
         s1 = s2 = 0;
         for (int w = 0; w < nwave; ++w) {
             const int64_t *r = part + 4 * w;
