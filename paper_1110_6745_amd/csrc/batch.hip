@@ -1347,12 +1347,17 @@ size_t job_bytes(const okpz_job &j, size_t nsamp)
 // the hand-over to the next sweep).
 constexpr double kNominalRate = 1.0e12;
 // Lattices with at least this many groups per sweep (4096 x 4096 and up)
-// run as plain per-lattice sweep launches on a second stream, next to the
+// run as plain per-lattice sweep launches on streams of their own, next to the
 // persistent launch: one large sweep fills the device by itself, while
 // through the claim words its groups would be handed out one atomic at a
 // time.
 constexpr int kGridGroups = 256;
 constexpr double kSweepLatency = 2.0e-5;
+// Streams for them.  A sweep of 4096 x 4096 has one workgroup per CU, which leaves half
+// the waves that a CU can hold idle; two jobs side by side fill them, a third covers
+// the ends of launches.  24 jobs, five of them 4096^2 at p < 1: 61.7 ms on one stream,
+// 53.7 on two, 52.6 on three, 53.1 on four.
+constexpr int kGridStreams = 3;
 
 struct okpz_server {
     size_t budget = 0, used = 0;
@@ -1369,8 +1374,8 @@ struct okpz_server {
     uint64_t *d_claim = nullptr;
     int32_t *d_sched = nullptr;
     hipStream_t stream = nullptr;
-    hipStream_t grid_stream = nullptr;  // plain sweeps of large lattices
-    int threads = 512, wgs = 0, cus = 0;  // two workgroups per CU without spills
+    hipStream_t grid_stream[kGridStreams] = {};  // plain sweeps of large lattices, made when needed
+    int threads = 0, wgs = 0, cus = 0;  // 0: by the open items
     int32_t cell_borders = OKPZ_CELLS_DEAD;  // for every job of the server
     std::chrono::steady_clock::time_point t0;
     int64_t quanta = 0, done = 0;
@@ -1492,9 +1497,9 @@ int admit(okpz_server *sv, ServeJob &J, int slot, double t)
     return OKPZ_OK;
 }
 
-// Advance a large job to sweep `stop` with plain per-lattice sweep launches
-// (and width launches at its sampling times) on the server's second stream.
-int run_grid(okpz_server *sv, ServeJob &J, int64_t stop)
+// One sweep of a large job as a plain per-lattice sweep launch (and a width
+// launch at a sampling time) on one of the server's streams for them.
+int grid_sweep(okpz_server *sv, ServeJob &J, hipStream_t stream)
 {
     const JobDesc &d = J.desc;
     okpz::Geometry g;
@@ -1514,33 +1519,31 @@ int run_grid(okpz_server *sv, ServeJob &J, int64_t stop)
     a.Tq = d.Tq;
     a.need_accept_draws = d.mode == okpz::core::kDraw ? 1 : 0;
     a.delayed_cells = sv->cell_borders == OKPZ_CELLS_DELAYED ? 1 : 0;
-    while (J.s < stop) {
-        const uint32_t sw = (uint32_t)J.s;
-        int32_t sx, sy;
-        okpz::block_shift(d.k0, d.k1, sw, g, &sx, &sy);
-        const int64_t x00 = (d.Lx - sx) % d.Lx, y00 = (d.Ly - sy) % d.Ly;
-        a.blk00 = (int32_t)((y00 / d.By) * d.nbx + x00 / d.Bx);
-        a.u00 = (int32_t)(x00 % d.Bx);
-        a.v00 = (int32_t)(y00 % d.By);
-        a.src = d.buf[J.cur];
-        a.dst = d.buf[J.cur ^ 1];
-        a.ox_src = J.ox;
-        a.sx = sx;
-        a.sy = sy;
-        a.s = sw;
-        hipError_t e = okpz::launch_sweep(a, 1024, sv->grid_stream);
-        if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "serve sweep: %s", hipGetErrorString(e));
-        J.cur ^= 1;
-        J.ox = sx;
-        J.s += 1;
-        if (J.next_sample < d.nsamp && J.times[J.next_sample] == J.s) {
-            const okpz::LatticeView v{d.buf[J.cur], d.Lx, d.Ly, d.W, J.ox};
-            // a sample is t, then what the width launch writes
-            e = okpz::launch_width(v, d.rows, d.h0, d.samples + 6 * (size_t)J.next_sample + 1, J.s,
-                                   sv->grid_stream);
-            if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "serve width: %s", hipGetErrorString(e));
-            ++J.next_sample;
-        }
+    const uint32_t sw = (uint32_t)J.s;
+    int32_t sx, sy;
+    okpz::block_shift(d.k0, d.k1, sw, g, &sx, &sy);
+    const int64_t x00 = (d.Lx - sx) % d.Lx, y00 = (d.Ly - sy) % d.Ly;
+    a.blk00 = (int32_t)((y00 / d.By) * d.nbx + x00 / d.Bx);
+    a.u00 = (int32_t)(x00 % d.Bx);
+    a.v00 = (int32_t)(y00 % d.By);
+    a.src = d.buf[J.cur];
+    a.dst = d.buf[J.cur ^ 1];
+    a.ox_src = J.ox;
+    a.sx = sx;
+    a.sy = sy;
+    a.s = sw;
+    hipError_t e = okpz::launch_sweep(a, 1024, stream);
+    if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "serve sweep: %s", hipGetErrorString(e));
+    J.cur ^= 1;
+    J.ox = sx;
+    J.s += 1;
+    if (J.next_sample < d.nsamp && J.times[J.next_sample] == J.s) {
+        const okpz::LatticeView v{d.buf[J.cur], d.Lx, d.Ly, d.W, J.ox};
+        // a sample is t, then what the width launch writes
+        e = okpz::launch_width(v, d.rows, d.h0, d.samples + 6 * (size_t)J.next_sample + 1, J.s,
+                               stream);
+        if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "serve width: %s", hipGetErrorString(e));
+        ++J.next_sample;
     }
     return OKPZ_OK;
 }
@@ -1585,9 +1588,7 @@ int okpz_serve_create(okpz_server **out, size_t hbm_budget, int32_t max_slots,
     (void)hipDeviceGetAttribute(&sv->cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (sv->cus <= 0) sv->cus = 256;
     e = hipStreamCreateWithFlags(&sv->stream, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&sv->grid_stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
-        if (sv->stream) (void)hipStreamDestroy(sv->stream);
         (void)hipFree(sv->mem);
         delete sv;
         return bfail(OKPZ_EDEVICE, "hipStreamCreate: %s", hipGetErrorString(e));
@@ -1684,8 +1685,8 @@ int okpz_serve_step(okpz_server *sv, int32_t *running, int32_t *waiting)
         }
     }
     // 2. quantum: every resident job advances by its share; small jobs in one
-    // persistent launch, large ones (J.grid) as plain sweep launches on the
-    // second stream at the same time
+    // persistent launch, large ones (J.grid) as plain sweep launches on their
+    // streams at the same time
     std::vector<JobDesc> desc(sv->max_slots);
     std::vector<uint64_t> claim(sv->max_slots, okpz::batch::kClosed);
     // items per sweep of each slot, then the scan order: oldest job first
@@ -1752,17 +1753,50 @@ int okpz_serve_step(okpz_server *sv, int32_t *running, int32_t *waiting)
         // beside plain sweeps, one persistent workgroup per CU leaves room for them
         const int wgs = sv->wgs ? sv->wgs : (grid_jobs.empty() ? 2 : 1) * sv->cus;
         if (items <= wgs) R.claim_flags |= okpz::batch::kClaimStay;
-        hipError_t e = launch_any(R, sv->threads, wgs);
+        // An item to a CU: all the waves of it that a CU can hold.  At 1024 / 512
+        // threads per workgroup: 8 jobs of 128^2 at p = 0.8, 600 sweeps, 11.8 / 15.3 ms, of
+        // 1024^2, 300 sweeps, 9.6 / 11.8 ms.  512 threads where two items share a CU:
+        // 6 jobs of 2048^2 9.9 / 9.6 ms.
+        const int threads = sv->threads ? sv->threads : items <= sv->cus ? 1024 : 512;
+        hipError_t e = launch_any(R, threads, wgs);
         if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "serve launch: %s", hipGetErrorString(e));
     }
     if (!grid_jobs.empty()) {
-        BHIP(hipStreamWaitEvent(sv->grid_stream, e0, 0));
+        // longest first, each on the stream with the least to do; the launches are
+        // queued a sweep of each stream in turn
+        auto work = [&](const std::pair<int64_t, int64_t> &gj) {
+            const ServeJob &J = sv->jobs[gj.first];
+            return (gj.second - J.s) * J.job.Lx * J.job.Ly;
+        };
+        std::stable_sort(grid_jobs.begin(), grid_jobs.end(),
+                         [&](const auto &x, const auto &y) { return work(x) > work(y); });
+        const int streams = std::min<int>(kGridStreams, (int)grid_jobs.size());
+        std::vector<std::deque<std::pair<int64_t, int64_t>>> queue(streams);
+        std::vector<int64_t> load(streams, 0);
         for (const auto &gj : grid_jobs) {
-            const int rc = run_grid(sv, sv->jobs[gj.first], gj.second);
-            if (rc != OKPZ_OK) return rc;
+            const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+            load[k] += work(gj);
+            queue[k].push_back(gj);
         }
-        BHIP(hipEventRecord(eg, sv->grid_stream));
-        BHIP(hipStreamWaitEvent(sv->stream, eg, 0));
+        for (int k = 0; k < streams; ++k) {
+            if (!sv->grid_stream[k]) BHIP(hipStreamCreateWithFlags(&sv->grid_stream[k], hipStreamNonBlocking));
+            BHIP(hipStreamWaitEvent(sv->grid_stream[k], e0, 0));
+        }
+        for (bool more = true; more;) {
+            more = false;
+            for (int k = 0; k < streams; ++k) {
+                if (queue[k].empty()) continue;
+                ServeJob &J = sv->jobs[queue[k].front().first];
+                const int rc = grid_sweep(sv, J, sv->grid_stream[k]);
+                if (rc != OKPZ_OK) return rc;
+                if (J.s >= queue[k].front().second) queue[k].pop_front();
+                more = true;
+            }
+        }
+        for (int k = 0; k < streams; ++k) {
+            BHIP(hipEventRecord(eg, sv->grid_stream[k]));
+            BHIP(hipStreamWaitEvent(sv->stream, eg, 0));
+        }
     }
     BHIP(hipEventRecord(e1, sv->stream));
     BHIP(hipStreamSynchronize(sv->stream));
@@ -1897,9 +1931,11 @@ int okpz_serve_free(okpz_server *sv)
     for (auto &J : sv->jobs)
         if (J.mem) (void)hipFree(J.mem);
     if (sv->mem) (void)hipFree(sv->mem);
-    if (sv->grid_stream) (void)hipStreamSynchronize(sv->grid_stream);
+    for (hipStream_t g : sv->grid_stream)
+        if (g) (void)hipStreamSynchronize(g);
     if (sv->stream) (void)hipStreamDestroy(sv->stream);
-    if (sv->grid_stream) (void)hipStreamDestroy(sv->grid_stream);
+    for (hipStream_t g : sv->grid_stream)
+        if (g) (void)hipStreamDestroy(g);
     delete sv;
     return OKPZ_OK;
 }
