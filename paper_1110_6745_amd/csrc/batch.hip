@@ -1355,8 +1355,10 @@ constexpr int kGridGroups = 256;
 constexpr double kSweepLatency = 2.0e-5;
 // Streams for them.  A sweep of 4096 x 4096 has one workgroup per CU, which leaves half
 // the waves that a CU can hold idle; two jobs side by side fill them, a third covers
-// the ends of launches.  24 jobs, five of them 4096^2 at p < 1: 61.7 ms on one stream,
-// 53.7 on two, 52.6 on three, 53.1 on four.
+// the ends of launches.  24 jobs, five of them 4096^2 at p < 1: 62.4 ms on one stream,
+// 47.5 on two, 45.5 on three, 45.8 on four.  They are made with the server's other
+// stream, so that each gets a hardware queue (made by the first quantum with such a
+// job they could share one with other streams: 52 to 54 ms on two or three).
 constexpr int kGridStreams = 3;
 
 struct okpz_server {
@@ -1374,7 +1376,7 @@ struct okpz_server {
     uint64_t *d_claim = nullptr;
     int32_t *d_sched = nullptr;
     hipStream_t stream = nullptr;
-    hipStream_t grid_stream[kGridStreams] = {};  // plain sweeps of large lattices, made when needed
+    hipStream_t grid_stream[kGridStreams] = {};  // plain sweeps of large lattices
     int threads = 0, wgs = 0, cus = 0;  // 0: by the open items
     int32_t cell_borders = OKPZ_CELLS_DEAD;  // for every job of the server
     std::chrono::steady_clock::time_point t0;
@@ -1588,7 +1590,12 @@ int okpz_serve_create(okpz_server **out, size_t hbm_budget, int32_t max_slots,
     (void)hipDeviceGetAttribute(&sv->cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (sv->cus <= 0) sv->cus = 256;
     e = hipStreamCreateWithFlags(&sv->stream, hipStreamNonBlocking);
+    for (hipStream_t &g : sv->grid_stream)
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&g, hipStreamNonBlocking);
     if (e != hipSuccess) {
+        if (sv->stream) (void)hipStreamDestroy(sv->stream);
+        for (hipStream_t g : sv->grid_stream)
+            if (g) (void)hipStreamDestroy(g);
         (void)hipFree(sv->mem);
         delete sv;
         return bfail(OKPZ_EDEVICE, "hipStreamCreate: %s", hipGetErrorString(e));
@@ -1778,10 +1785,7 @@ int okpz_serve_step(okpz_server *sv, int32_t *running, int32_t *waiting)
             load[k] += work(gj);
             queue[k].push_back(gj);
         }
-        for (int k = 0; k < streams; ++k) {
-            if (!sv->grid_stream[k]) BHIP(hipStreamCreateWithFlags(&sv->grid_stream[k], hipStreamNonBlocking));
-            BHIP(hipStreamWaitEvent(sv->grid_stream[k], e0, 0));
-        }
+        for (int k = 0; k < streams; ++k) BHIP(hipStreamWaitEvent(sv->grid_stream[k], e0, 0));
         for (bool more = true; more;) {
             more = false;
             for (int k = 0; k < streams; ++k) {

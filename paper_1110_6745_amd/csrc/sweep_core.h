@@ -9,7 +9,7 @@
 //      funnel shift of two stored words per 32 sites) and expanded to one byte
 //      per site;
 //   2. C*C = 64 steps in LDS: per step one cell origin per block, one site per
-//      8x8 thread cell, the four-bond test on a five-bit code and, when
+//      8x8 thread cell, the four-bond test on three two-bit bytes and, when
 //      accepted, three byte stores;
 //   3. LDS -> HBM: bytes are packed back to bits and each block is written
 //      *aligned* into the other lattice copy, whose stored columns start at
