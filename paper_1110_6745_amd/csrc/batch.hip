@@ -40,6 +40,7 @@
 #include <string>
 #include <vector>
 
+#include "claim_word.h"
 #include "host_logic.h"
 #include "okpz.h"
 #include "state_io.h"
@@ -79,15 +80,6 @@ struct Control {
     int32_t finished;   // jobs that reached their stop target
     int32_t error;      // 1: watchdog
 };
-
-// claim[r] = (sweep << 32) | next item to hand out; job r has an open item
-// while the low word is below nitems[r] (its items per sweep).  A finished or empty job holds
-// kClosed in the low word.  A scan can see a word open that is exhausted or
-// closed by the time the wave's fetch-and-add lands; such late increments
-// are at most two (one claim) per workgroup per word value, so the low word
-// never carries into the sweep number (kClosed + 2 workgroups < 2^32).  A job
-// advanced by a team (kClaimStay) holds kTeam: nothing to claim, but its members go on.
-constexpr uint32_t kClosed = 0x80000000u, kTeam = 0x40000000u;
 
 // Polled words (claim words, counters) are read and published at system
 // scope, which bypasses the per-XCD caches: a poller never spins on a stale
@@ -286,7 +278,7 @@ __device__ bool await_sweep(uint64_t *word, uint32_t s, Control *ctl, uint64_t i
     uint64_t seen = 0, idle = 0;
     for (uint32_t polls = 1;; ++polls) {
         const uint64_t w = ld_rlx(word);
-        if ((uint32_t)(w >> 32) != s) return (uint32_t)w >= kTeam && (uint32_t)w < kClosed;
+        if ((uint32_t)(w >> 32) != s) return team_goes_on(w, s);
         __builtin_amdgcn_s_sleep(4);
         if (polls % 64 != 0) continue;
         if (__hip_atomic_load(&ctl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0) return false;
