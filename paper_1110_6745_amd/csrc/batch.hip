@@ -221,8 +221,8 @@ constexpr int kChainSweeps = 32;
 constexpr int kMostPause = 128;  // units of 16 x 64 cycles
 
 // Wave 0 looks for an open item and claims items_per_claim of them (fewer
-// if the sweep has fewer left): first of job `prefer` (the job of the
-// workgroup's previous claim, -1 for none) with one fetch-and-add and no
+// if the sweep has fewer left): first of job `prefer` (preferred_job,
+// -1 for none) with one fetch-and-add and no
 // scan, else trying jobs in priority order (order[0] first).  Returns the
 // job index and writes the claimed (sweep << 32 | first item), or -1.
 __device__ int find_and_claim(uint64_t *claim, const int32_t *nitems, const int32_t *order,
@@ -320,14 +320,14 @@ __global__ __launch_bounds__(kThreads, kThreads / 128) void batch_kernel(const J
     const int32_t *nitems = sched, *order = sched + njobs;
     const uint64_t t_begin = budget ? (uint64_t)wall_clock64() : 0;
     int pause = 1;  // units of 16 x 64 cycles (thread 0)
-    int last = -1;  // job of the previous claim (wave 0, uniform)
+    int last = -1;  // job to try first (wave 0, uniform)
 
     while (true) {
         if (tid < 64) {
             uint64_t w = 0;
             const bool over = budget && (uint64_t)wall_clock64() - t_begin > budget;
             int r = over ? -1 : find_and_claim(claim, nitems, order, njobs, last, claim_flags, &w);
-            if (r >= 0) last = r;
+            last = preferred_job(r);
             if (tid == 0) {
                 if (over) {
                     r = -1;

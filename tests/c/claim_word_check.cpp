@@ -1,8 +1,9 @@
 // CPU check of the batch kernel's claim-word rules (csrc/claim_word.h): who goes on
-// as a team after a sweep.  Prints "claim words ok" or the first fault.
+// as a team after a sweep, and what looks for work add to a word.  Prints "claim words
+// ok" or the first fault.
 #include <cstdio>
 #include <cstdlib>
-#include <vector>
+#include <initializer_list>
 
 #include "claim_word.h"
 
@@ -43,6 +44,22 @@ int main()
         w = word(2, kTeam);                    // completed by workgroups that all stayed
         require(!team_goes_on(w, 0), "a waiter of sweep 0 joins the team of sweep 2");
     }
+    // Workgroups that look on for work after their job's end, while one other job
+    // still runs: the closed word must not creep towards the next sweep's number.
+    {
+        const int job = 3, looks = 100000, workgroups = 512;
+        uint64_t w = word(40, kClosed);
+        for (int g = 0; g < workgroups; ++g) {
+            int prefer = job;  // claimed from it last
+            for (int i = 0; i < looks; ++i) {
+                if (prefer >= 0) w += 2;  // the try of two items without a look
+                prefer = preferred_job(-1);
+            }
+        }
+        require(w >> 32 == 40 && (uint32_t)w >= kClosed, "looks for work reopen a finished job");
+        require((uint32_t)w - kClosed <= 2u * workgroups, "looks for work add to a closed word without bound");
+    }
+    require(preferred_job(5) == 5 && preferred_job(0) == 0, "the previous claim's job is not preferred");
     std::printf("claim words ok\n");
     return 0;
 }
