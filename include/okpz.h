@@ -112,7 +112,7 @@ int okpz_w2(okpz_sim *s, double *w2);
  * (radix 2 for a power-of-two side, Bluestein's chirp-z form otherwise).
  * The first call allocates at most min(32 MiB, Lx*Ly/4) + 40*max(Lx,Ly)
  * bytes of device scratch (plus 128*max(Lx,Ly) when a side is not a power of
- * two), kept until okpz_free.  Synchronous. */
+ * two, and up to 2 KiB of alignment), kept until okpz_free.  Synchronous. */
 int okpz_psd(okpz_sim *s, double *sx, double *sy);
 
 /* For callers that cannot allocate device memory (code that must not call

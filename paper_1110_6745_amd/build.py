@@ -12,7 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = ["api.hip", "sweep.hip", "sweep_chain.hip", "width.hip", "psd.hip", "batch.hip", "state_io.hip"]
-HOST_SOURCES = ["host_logic.cpp"]  # plain C++, no device code
+HOST_SOURCES = ["host_logic.cpp", "psd_plan.cpp"]  # plain C++, no device code
 LIB = os.path.join(HERE, "libokpz.so")
 RESOURCES = os.path.join(HERE, "_build", "kernel_resources.json")
 _REMARK = re.compile(r"remark:\s+(Function Name|TotalSGPRs|VGPRs|AGPRs|ScratchSize \[bytes/lane\]|"

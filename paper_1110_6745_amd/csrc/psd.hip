@@ -32,14 +32,6 @@
 namespace okpz {
 namespace {
 
-constexpr int kPlaneThreads = 512;
-constexpr int kPlaneWaves = kPlaneThreads / 64;
-constexpr int kStripWords = 256;          // words of a row a wavefront takes: four per lane
-constexpr int kStripCols = 32 * kStripWords;
-constexpr int kGroupRows = 8;             // rows per carry-save group
-constexpr int kMaxWaveRows = 255 * kGroupRows;  // byte lanes count up to 255 groups
-constexpr int kPlaneTarget = 512;         // workgroups of the plane pass
-constexpr int kProfThreads = 256;
 constexpr int kFftThreads = 512;
 constexpr int kWideThreads = 256;
 constexpr int kTile = 4096;               // complex fp64 values per LDS tile
@@ -74,10 +66,15 @@ __device__ __forceinline__ int32_t wave_sum63(int32_t x)
 // part before the stored column xs0 of physical column 0 (|d|, |q| <= 8192).
 // A bit's weight within its word is read off five masked popcounts.
 // kVec: W is a multiple of four (16-byte loads, every lane has four words or none).
+// kTall (PsdPlan::tall): rowsum[y] and rowsum[2 Ly + y], zero before, get the strips' sums of
+// P to the row's end and of q instead, by one atomic addition each per strip and row
+// (16 bytes beside the 1024 read), and a wavefront adds its column counters up
+// every kMaxWaveRows rows.
 // The next eight rows are in flight while eight are counted (sixteen left two waves per
 // SIMD for registers, three hide more).
-template <bool kVec>
-__global__ __launch_bounds__(kPlaneThreads, kVec ? 4 : 3) void plane_kernel(LatticeView v, int32_t R, int32_t *partial, int2 *rowpart)
+template <bool kVec, bool kTall>
+__global__ __launch_bounds__(kPlaneThreads, kVec ? 4 : 3) void plane_kernel(LatticeView v, int32_t R, int32_t *partial,
+                                                                            int2 *rowpart, int64_t *rowsum)
 {
     // counts of a lane's 128 columns, column j of lane l at 65 j + l: neither the
     // lanes' sums nor the ordered read meet in a bank
@@ -102,14 +99,18 @@ __global__ __launch_bounds__(kPlaneThreads, kVec ? 4 : 3) void plane_kernel(Latt
     for (int t = 0; t < 4; ++t) nbefore += t < nw ? __popc(mask[t]) : 0;
 
     const int rw = R / kPlaneWaves;
-    const int ya = min(v.Ly, (int)blockIdx.y * R + wave * rw), yb = min(v.Ly, ya + rw);
+    const int y_lo = min(v.Ly, (int)blockIdx.y * R + wave * rw), y_hi = min(v.Ly, y_lo + rw);
+    int ya = y_lo, yb = kTall ? min(y_hi, y_lo + kMaxWaveRows) : y_hi;
     uint32_t ones[4], twos[4], fours[4], acc[4][8];
+    auto clear = [&] {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        ones[t] = twos[t] = fours[t] = 0u;
+        for (int t = 0; t < 4; ++t) {
+            ones[t] = twos[t] = fours[t] = 0u;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[t][j] = 0u;
-    }
+            for (int j = 0; j < 8; ++j) acc[t][j] = 0u;
+        }
+    };
+    clear();
     // (rows and words beyond the ends are read from inside, and zeroed before use)
     const uint32_t *word0 = v.planes + (kVec ? min(k0, v.W - 4) : 0);
     auto load = [&](int y0, uint32_t w[kGroupRows][4]) {
@@ -168,7 +169,16 @@ __global__ __launch_bounds__(kPlaneThreads, kVec ? 4 : 3) void plane_kernel(Latt
                 pack += d << 16;
             }
             const int32_t rs = wave_sum63(!kVec || nw ? r : 0), ps = wave_sum63(!kVec || nw ? pack : 0);
-            if (lane == 63 && y0 + i < yb) rowpart[(size_t)strip * v.Ly + y0 + i] = make_int2(rs, ps);
+            if (lane == 63 && y0 + i < yb) {
+                if (kTall) {
+                    const int32_t ds = (int16_t)ps;
+                    unsigned long long *sum = reinterpret_cast<unsigned long long *>(rowsum) + y0 + i;
+                    atomicAdd(sum, (unsigned long long)(rs + (int64_t)ds * (v.Lx - E)));
+                    atomicAdd(sum + 2 * (size_t)v.Ly, (unsigned long long)(int64_t)((ps - ds) >> 16));
+                } else {
+                    rowpart[(size_t)strip * v.Ly + y0 + i] = make_int2(rs, ps);
+                }
+            }
         }
         // columns
 #pragma unroll
@@ -185,7 +195,7 @@ __global__ __launch_bounds__(kPlaneThreads, kVec ? 4 : 3) void plane_kernel(Latt
             for (int j = 0; j < 8; ++j) acc[t][j] += (eights >> j) & 0x01010101u;
         }
     };
-    if (ya < yb) {
+    auto rows = [&] {  // ya .. yb
         uint32_t w0[kGroupRows][4], w1[kGroupRows][4];
         load(ya, w0);
         for (int y = ya; y < yb; y += 2 * kGroupRows) {
@@ -194,17 +204,32 @@ __global__ __launch_bounds__(kPlaneThreads, kVec ? 4 : 3) void plane_kernel(Latt
             load(y + 2 * kGroupRows, w0);
             if (y + kGroupRows < yb) count(y + kGroupRows, w1);
         }
-    }
-    __syncthreads();  // cols is zero
+    };
+    auto add_up = [&] {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        if (t >= nw || ya >= yb) continue;
+        for (int t = 0; t < 4; ++t) {
+            if (t >= nw || ya >= yb) continue;
 #pragma unroll
-        for (int b = 0; b < 32; ++b) {
-            const uint32_t n = 8 * ((acc[t][b & 7] >> (b & ~7)) & 0xffu) + 4 * ((fours[t] >> b) & 1u) +
-                               2 * ((twos[t] >> b) & 1u) + ((ones[t] >> b) & 1u);
-            atomicAdd(cols + 65 * (32 * t + b) + lane, n);
+            for (int b = 0; b < 32; ++b) {
+                const uint32_t n = 8 * ((acc[t][b & 7] >> (b & ~7)) & 0xffu) + 4 * ((fours[t] >> b) & 1u) +
+                                   2 * ((twos[t] >> b) & 1u) + ((ones[t] >> b) & 1u);
+                atomicAdd(cols + 65 * (32 * t + b) + lane, n);
+            }
         }
+    };
+    if (kTall) {
+        __syncthreads();  // cols is zero
+        while (ya < yb) {
+            rows();
+            add_up();
+            clear();
+            ya = yb;
+            yb = min(y_hi, ya + kMaxWaveRows);
+        }
+    } else {
+        if (ya < yb) rows();
+        __syncthreads();  // cols is zero
+        add_up();
     }
     __syncthreads();
     const int c0 = strip * kStripCols;
@@ -232,10 +257,17 @@ struct Profiles {
     const int2 *rowpart;
     int32_t nch;
     int32_t *prefix[2];  // per axis (x, y)
-    int64_t *extra;
+    int64_t *extra;          // at first the rows' sums of the tall plane pass, if rowpart is null
     int64_t *blk[2];
     int32_t nblk[2];
 };
+
+// rows[0, Ly) and rows[2 Ly, 3 Ly) to zero, for the tall plane pass.
+__global__ __launch_bounds__(kProfThreads) void clear_rows_kernel(int64_t *rows, int32_t Ly)
+{
+    const int i = blockIdx.x * kProfThreads + threadIdx.x;
+    if (i < Ly) rows[i] = rows[2 * (size_t)Ly + i] = 0;
+}
 
 __device__ __forceinline__ int side(const LatticeView &v, int axis) { return axis ? v.Ly : v.Lx; }
 
@@ -261,7 +293,11 @@ __global__ __launch_bounds__(kProfThreads) void profile_steps_kernel(Profiles p)
         } else {
             // sum of P = sum of Q - Lx Q(xs0), Q the stored-order prefix
             int64_t q0 = 0;
-            for (int s = 0; s * kStripCols < v.Lx; ++s) {
+            if (!p.rowpart) {
+                e = p.extra[i];
+                q0 = p.extra[2 * (size_t)v.Ly + i];
+            }
+            for (int s = 0; p.rowpart && s * kStripCols < v.Lx; ++s) {
                 const int2 r = p.rowpart[(size_t)s * v.Ly + i];
                 const int32_t ds = (int16_t)r.y;
                 e += r.x + (int64_t)ds * (v.Lx - min(v.Lx, (s + 1) * kStripCols));
@@ -583,16 +619,6 @@ int log2_exact(int64_t n)
     return l;
 }
 
-bool pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
-
-// Bluestein length for a side n: the power of two M >= 2n - 1.
-int64_t conv_len(int64_t n)
-{
-    int64_t M = 1;
-    while (M < 2 * n - 1) M <<= 1;
-    return M;
-}
-
 // The transforms and spectra of the axes in [first, first + count).
 hipError_t launch_transforms(const Axes &axes, int count, hipStream_t st)
 {
@@ -629,78 +655,26 @@ hipError_t launch_transforms(const Axes &axes, int count, hipStream_t st)
     return hipGetLastError();
 }
 
-int32_t blocks_of(int64_t n) { return (int32_t)((n + kProfThreads - 1) / kProfThreads); }
-
-// Scratch layout for R rows per workgroup of the plane pass (a multiple of
-// kPlaneWaves * kGroupRows).  The transforms take the place of the plane pass's
-// parts, which are added up by then.  together: both axes'
-// Bluestein buffers at once.
-PsdPlan plan_with_rows(int64_t Lx, int64_t Ly, int64_t R, bool together)
-{
-    PsdPlan p{};
-    p.R = (int32_t)R;
-    p.nch = (int32_t)((Ly + R - 1) / R);
-    auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-    const size_t strips = (size_t)((Lx + kStripCols - 1) / kStripCols);
-    p.off_rowpart = al((size_t)p.nch * Lx * 4);
-    const size_t parts = p.off_rowpart + al(strips * (size_t)Ly * 8);
-    p.off_zx = 0;
-    p.off_zy = pow2(Lx) ? al((size_t)Lx * 16) : 0;
-    p.off_conv = p.off_zy + (pow2(Ly) ? al((size_t)Ly * 16) : 0);
-    const size_t Mx = pow2(Lx) ? 0 : (size_t)conv_len(Lx), My = pow2(Ly) ? 0 : (size_t)conv_len(Ly);
-    p.together = together || Mx == 0 || My == 0;
-    const size_t conv = p.together ? Mx + My : (Mx > My ? Mx : My);
-    const size_t work = p.off_conv + al(2 * conv * 16);
-    p.off_spec = parts > work ? parts : work;
-    p.off_prefix = p.off_spec + al((size_t)(Lx / 2 + 1 + Ly / 2 + 1) * 8);
-    p.off_blk = p.off_prefix + al((size_t)Lx * 4);
-    p.bytes = p.off_blk + al((2 * ((size_t)blocks_of(Lx) + blocks_of(Ly))) * 8);
-    return p;
-}
-
-constexpr int64_t kRowStep = kPlaneWaves * kGroupRows;
-constexpr int64_t kMaxRows = (int64_t)kPlaneWaves * kMaxWaveRows;
-
 }  // namespace
-
-PsdPlan psd_plan_capped(int64_t Lx, int64_t Ly, size_t max_bytes)
-{
-    // enough workgroups to fill the device, then fewer and taller ones until the
-    // parts fit the bytes; both axes' transforms at once if they fit too
-    const int64_t strips = (Lx + kStripCols - 1) / kStripCols;
-    const int64_t chunks = (kPlaneTarget + strips - 1) / strips;
-    int64_t R = ((Ly + chunks - 1) / chunks + kRowStep - 1) / kRowStep * kRowStep;
-    if (R > kMaxRows) R = kMaxRows;
-    for (;; R = 2 * R < kMaxRows ? 2 * R : kMaxRows) {
-        for (int together = 1; together >= 0; --together) {
-            const PsdPlan p = plan_with_rows(Lx, Ly, R, together != 0);
-            if (p.bytes <= max_bytes) return p;
-            if (!together && (R >= Ly || R >= kMaxRows)) return p;  // the caller checks .bytes
-        }
-    }
-}
-
-// Within min(32 MiB, Lx Ly / 4) + 40 max(Lx, Ly) bytes, plus 128 max(Lx, Ly) when a
-// side is not a power of two (and the pieces' alignment).
-PsdPlan psd_plan(int64_t Lx, int64_t Ly)
-{
-    const size_t n = (size_t)Lx * Ly, most = (size_t)(Lx > Ly ? Lx : Ly);
-    const size_t parts = n / 4 < (size_t(32) << 20) ? n / 4 : size_t(32) << 20;
-    return psd_plan_capped(Lx, Ly, parts + 40 * most + (pow2(Lx) && pow2(Ly) ? 0 : 128 * most) + 2048);
-}
 
 hipError_t launch_psd(const LatticeView &v, const PsdPlan &p, int64_t *rows, void *scratch, hipStream_t st)
 {
     char *base = static_cast<char *>(scratch);
     int32_t *partial = reinterpret_cast<int32_t *>(base);
-    int2 *rowpart = reinterpret_cast<int2 *>(base + p.off_rowpart);
-    const int strips = (v.Lx + kStripCols - 1) / kStripCols;
-    if ((v.W & 3) == 0)
-        hipLaunchKernelGGL(plane_kernel<true>, dim3(strips, p.nch), dim3(kPlaneThreads), 0, st, v, p.R, partial,
-                           rowpart);
-    else
-        hipLaunchKernelGGL(plane_kernel<false>, dim3(strips, p.nch), dim3(kPlaneThreads), 0, st, v, p.R, partial,
-                           rowpart);
+    int2 *rowpart = p.tall ? nullptr : reinterpret_cast<int2 *>(base + p.off_rowpart);
+    const dim3 grid((v.Lx + kStripCols - 1) / kStripCols, p.nch), threads(kPlaneThreads);
+    const bool vec = (v.W & 3) == 0;
+    if (p.tall) {
+        hipLaunchKernelGGL(clear_rows_kernel, dim3((unsigned)blocks_of(v.Ly)), dim3(kProfThreads), 0, st, rows, v.Ly);
+        if (vec)
+            hipLaunchKernelGGL((plane_kernel<true, true>), grid, threads, 0, st, v, p.R, partial, rowpart, rows);
+        else
+            hipLaunchKernelGGL((plane_kernel<false, true>), grid, threads, 0, st, v, p.R, partial, rowpart, rows);
+    } else if (vec) {
+        hipLaunchKernelGGL((plane_kernel<true, false>), grid, threads, 0, st, v, p.R, partial, rowpart, rows);
+    } else {
+        hipLaunchKernelGGL((plane_kernel<false, false>), grid, threads, 0, st, v, p.R, partial, rowpart, rows);
+    }
 
     Profiles pr{};
     pr.v = v;
