@@ -112,7 +112,8 @@ int okpz_w2(okpz_sim *s, double *w2);
  * (radix 2 for a power-of-two side, Bluestein's chirp-z form otherwise).
  * The first call allocates at most min(32 MiB, Lx*Ly/4) + 40*max(Lx,Ly)
  * bytes of device scratch (plus 128*max(Lx,Ly) when a side is not a power of
- * two, and up to 2 KiB of alignment), kept until okpz_free.  Synchronous. */
+ * two, and up to 2 KiB of alignment) and, for spectra of at most 1 MiB, as much
+ * pinned host memory; both are kept until okpz_free.  Synchronous. */
 int okpz_psd(okpz_sim *s, double *sx, double *sy);
 
 /* For callers that cannot allocate device memory (code that must not call
@@ -122,8 +123,9 @@ int okpz_psd(okpz_sim *s, double *sx, double *sy);
  * memory, one per GPU, reserved when the library's code is loaded and held
  * until the process ends (its address is looked up once per device when the
  * first handle is created there).  Lattices with a side above 2^17 are
- * rejected with OKPZ_EINVAL.  No call allocates device memory; the result
- * copies to sx and sy go through the HIP runtime's own staging.  Every call
+ * rejected with OKPZ_EINVAL.  No call allocates device or pinned host memory;
+ * the result copies to sx and sy go through the HIP runtime's own staging (or
+ * the pinned buffer of an earlier okpz_psd of the handle).  Every call
  * on one GPU uses the same array and nothing in it is kept between calls:
  * calls that overlap on one GPU (handles driven from different host threads)
  * race and must be serialised by the caller.  Synchronous. */

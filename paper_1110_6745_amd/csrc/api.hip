@@ -569,14 +569,16 @@ int okpz_w2(okpz_sim *s, double *w2)
     return OKPZ_OK;
 }
 
-// The two spectra, one after the other at spec on the device, to the host.
-static int copy_spectra(okpz_sim *s, const char *spec, double *sx, double *sy)
+// The two spectra, one after the other at spec on the device, to the host.  make_pinned:
+// the handle's pinned buffer may be allocated (okpz_psd); otherwise it serves only if
+// it is there.
+static int copy_spectra(okpz_sim *s, const char *spec, double *sx, double *sy, bool make_pinned)
 {
     const size_t bx = ((size_t)s->Lx / 2 + 1) * 8, by = ((size_t)s->Ly / 2 + 1) * 8;
     // Up to a mebibyte in one copy to pinned memory: two copies to the caller's
     // (pageable) arrays take about 60 us of a small lattice's call.
     if (bx + by <= kPinnedSpectra) {
-        if (!s->h_spec && hipHostMalloc(&s->h_spec, bx + by) != hipSuccess) {
+        if (!s->h_spec && make_pinned && hipHostMalloc(&s->h_spec, bx + by) != hipSuccess) {
             (void)hipGetLastError();
             s->h_spec = nullptr;
         }
@@ -607,7 +609,7 @@ int okpz_psd(okpz_sim *s, double *sx, double *sy)
     }
     okpz::LatticeView v{s->buf[s->cur], (int32_t)s->Lx, (int32_t)s->Ly, s->W, s->ox};
     HIP_TRY(okpz::launch_psd(v, p, s->d_rows, s->psd_mem, s->stream));
-    return copy_spectra(s, static_cast<const char *>(s->psd_mem) + p.off_spec, sx, sy);
+    return copy_spectra(s, static_cast<const char *>(s->psd_mem) + p.off_spec, sx, sy, true);
 }
 
 int okpz_psd_noalloc(okpz_sim *s, double *sx, double *sy)
@@ -627,7 +629,7 @@ int okpz_psd_noalloc(okpz_sim *s, double *sx, double *sy)
     if (!mem) return hip_fail(se, "hipGetSymbolAddress(scratch)");
     okpz::LatticeView v{s->buf[s->cur], (int32_t)s->Lx, (int32_t)s->Ly, s->W, s->ox};
     HIP_TRY(okpz::launch_psd(v, p, s->d_rows, mem, s->stream));
-    return copy_spectra(s, static_cast<const char *>(mem) + p.off_spec, sx, sy);
+    return copy_spectra(s, static_cast<const char *>(mem) + p.off_spec, sx, sy, false);
 }
 
 int okpz_time(const okpz_sim *s, int64_t *t)
