@@ -53,7 +53,8 @@ size_t okpz_required_bytes(int64_t Lx, int64_t Ly);
  * state h = (x+y) mod 2 (Sec. III: W^2(L,0) = 1/4), time t = 0, attachment
  * probability p and detachment probability q in [0,1] (Eq. (1)), and the
  * seed that keys every random decision.  The library allocates device memory
- * and a stream.  *out receives the handle (NULL on error). */
+ * and a stream (and, for every handle, 64 bytes of pinned host memory for its
+ * measurements, 4 KiB for every 64 handles).  *out receives the handle (NULL on error). */
 int okpz_init(okpz_sim **out, int64_t Lx, int64_t Ly, double p, double q, uint64_t seed);
 
 /* As okpz_init, but on caller-owned device memory (dev_buf, at least

@@ -40,7 +40,7 @@ struct okpz_sim {
     int threads;  // sweep workgroup size (execution mapping only)
     int32_t cell_borders;  // OKPZ_CELLS_DEAD or OKPZ_CELLS_DELAYED
     void *psd_mem;  // spectrum scratch, allocated by the first okpz_psd
-    int64_t *h_out; // pinned host memory that the width kernel writes its sums to
+    int64_t *h_out; // pinned host block that the width kernel writes its sums to (nullptr: none left)
     void *h_spec;   // pinned host memory for the spectra of short sides
     void *io_mem;   // staging of lattice transfers, allocated by the first one
     int cus;        // the device's compute units
@@ -142,13 +142,67 @@ int alloc_state(okpz_sim *s, void *dev_buf, size_t bytes, void *stream)
     return OKPZ_OK;
 }
 
+// Pinned host memory for the words of a measurement: a 64-byte block per handle, from
+// slabs of 64 blocks (a pinned allocation and its release of their own cost a handle
+// about 100 us, a twentieth of a 4096 x 4096 state's way through the host).  A slab is of
+// one device, and is given back with its last block.
+struct PinnedSlab {
+    PinnedSlab *next;
+    int64_t *words;
+    int device;
+    uint64_t used;  // bit per block
+};
+constexpr int kBlockWords = 8, kSlabBlocks = 64;
+std::mutex g_slab_mu;
+PinnedSlab *g_slabs;
+
+// nullptr if there is no memory for it (measurements then copy from d_out).
+int64_t *take_block(int device)
+{
+    std::lock_guard<std::mutex> lock(g_slab_mu);
+    PinnedSlab *f = g_slabs;
+    while (f && (f->device != device || f->used == ~uint64_t(0))) f = f->next;
+    if (!f) {
+        f = new (std::nothrow) PinnedSlab{g_slabs, nullptr, device, 0};
+        if (!f) return nullptr;
+        if (hipHostMalloc(reinterpret_cast<void **>(&f->words), kSlabBlocks * kBlockWords * sizeof(int64_t)) !=
+            hipSuccess) {
+            (void)hipGetLastError();
+            delete f;
+            return nullptr;
+        }
+        g_slabs = f;
+    }
+    const int i = __builtin_ctzll(~f->used);
+    f->used |= uint64_t(1) << i;
+    return f->words + i * kBlockWords;
+}
+
+// No kernel may still write the block.
+void give_block(int64_t *block)
+{
+    if (!block) return;
+    std::lock_guard<std::mutex> lock(g_slab_mu);
+    for (PinnedSlab **at = &g_slabs; *at; at = &(*at)->next) {
+        PinnedSlab *f = *at;
+        if (block < f->words || block >= f->words + kSlabBlocks * kBlockWords) continue;
+        f->used &= ~(uint64_t(1) << ((block - f->words) / kBlockWords));
+        if (f->used == 0) {
+            *at = f->next;
+            (void)hipHostFree(f->words);
+            delete f;
+        }
+        return;
+    }
+}
+
 void release(okpz_sim *s)
 {
     if (!s) return;
     (void)hipStreamSynchronize(s->stream);
     if (s->psd_mem) (void)hipFree(s->psd_mem);
     if (s->io_mem) (void)hipFree(s->io_mem);
-    if (s->h_out) (void)hipHostFree(s->h_out);
+    give_block(s->h_out);
     if (s->h_spec) (void)hipHostFree(s->h_spec);
     if (s->own_mem && s->mem) (void)hipFree(s->mem);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
@@ -238,6 +292,7 @@ int make_sim(okpz_sim **out, int64_t Lx, int64_t Ly, double p, double q, uint64_
         delete s;
         return rc;
     }
+    s->h_out = take_block(s->device);  // here, not in the first measurement
     *out = s;
     return OKPZ_OK;
 }
@@ -518,10 +573,6 @@ static int measure(okpz_sim *s, __int128 *S1r, __int128 *S2r, int64_t *H0)
     okpz::LatticeView v{s->buf[s->cur], (int32_t)s->Lx, (int32_t)s->Ly, s->W, s->ox};
     // five words straight to the host: two copies of a few bytes cost as much as
     // the kernel on a small lattice
-    if (!s->h_out && hipHostMalloc(reinterpret_cast<void **>(&s->h_out), 8 * sizeof(int64_t)) != hipSuccess) {
-        (void)hipGetLastError();
-        s->h_out = nullptr;
-    }
     int64_t host[5];
     HIP_TRY(okpz::launch_width(v, s->d_rows, s->d_h0, s->h_out ? s->h_out : s->d_out, -1, s->stream));
     if (!s->h_out) HIP_TRY(hipMemcpyAsync(host, s->d_out, sizeof host, hipMemcpyDeviceToHost, s->stream));

@@ -22,7 +22,7 @@ Lx, Ly = 320, 256
 make = okpz.okpz_init if {copies} == 2 else okpz.okpz_init_in_place
 other = make(Lx, Ly, 1.0, 0.0, 2)
 other.sweep(2)
-other.psd_noalloc()  # the runtime's own first-use work is done by another handle
+other.width(), other.w2(), other.psd_noalloc()  # the runtime's own first-use work is done by another handle
 sim = make(Lx, Ly, 1.0, 0.0, 1)
 sim.sweep(3)
 os.write(2, b"\\nMARK begin\\n")
@@ -34,6 +34,8 @@ print("child ok", flush=True)
 
 CALLS = {
     "psd_noalloc": "sim.psd_noalloc()",
+    "width": "sim.width()",
+    "w2": "sim.w2()",
 }
 
 
@@ -51,3 +53,29 @@ def test_first_call_allocates_nothing(call, copies):
     found = re.findall(r"hip\w*(?:Malloc|HostAlloc|HostRegister|Free)\w* *\(", during)
     assert not found, found
     assert re.search(r"hipMalloc *\(", log), "the log would not show an allocation"
+
+
+def test_measurements_of_many_handles():
+    # more handles than one pinned slab serves, freed and made again in between
+    import oracle
+    from paper_1110_6745_amd import okpz
+
+    Lx, Ly = 64, 32
+
+    def made(seed):
+        sim = okpz.okpz_init(Lx, Ly, 0.9, 0.2, seed)
+        sim.sweep(1 + seed % 3)
+        return sim
+
+    def want(seed):
+        lat = oracle.flat(Lx, Ly)
+        return oracle.width_sums(lat, oracle.run(lat, 0.9, 0.2, seed, 0, 1 + seed % 3, 0))
+
+    sims = {seed: made(seed) for seed in range(130)}
+    for seed in range(0, 130, 2):
+        sims.pop(seed).free()
+    sims.update({seed: made(seed) for seed in range(200, 240)})
+    for seed, sim in sims.items():
+        assert sim.width() == want(seed), seed
+    for sim in sims.values():
+        sim.free()
