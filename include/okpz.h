@@ -127,9 +127,9 @@ int okpz_psd(okpz_sim *s, double *sx, double *sy);
  * rejected with OKPZ_EINVAL.  No call allocates device or pinned host memory;
  * the result copies to sx and sy go through the HIP runtime's own staging (or
  * the pinned buffer of an earlier okpz_psd of the handle).  Every call
- * on one GPU uses the same array and nothing in it is kept between calls:
- * calls that overlap on one GPU (handles driven from different host threads)
- * race and must be serialised by the caller.  Synchronous. */
+ * on one GPU uses the same array, as the lattice transfers below do, and
+ * nothing in it is kept between calls: calls from different host threads
+ * take turns at it.  Synchronous. */
 int okpz_psd_noalloc(okpz_sim *s, double *sx, double *sy);
 
 /* Current time in MCS, and the absolute height H0 = h(0,0) (synchronous). */
@@ -140,7 +140,9 @@ int okpz_h0(okpz_sim *s, int64_t *h0);
 void *okpz_stream(const okpz_sim *s);
 
 /* Copy the whole lattice to host memory in the canonical layout
- * (bytes >= Lx*Ly).  Synchronous. */
+ * (bytes >= Lx*Ly).  Synchronous.  Lattice transfers (these calls,
+ * okpz_set_lattice and okpz_batch_get_lattice) allocate no device memory:
+ * they are staged in the GPU's fixed array of okpz_psd_noalloc, in turns. */
 int okpz_get_lattice(okpz_sim *s, uint8_t *host, size_t bytes);
 
 /* Copy rows y0 .. y0+nrows-1 (mod Ly) in the canonical layout

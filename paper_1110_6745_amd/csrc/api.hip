@@ -15,6 +15,7 @@
 #include "okpz_internal.h"
 #include "psd.h"
 #include "state_io.h"
+#include "static_scratch.h"
 #include "width.h"
 
 struct okpz_sim {
@@ -42,9 +43,8 @@ struct okpz_sim {
     void *psd_mem;  // spectrum scratch, allocated by the first okpz_psd
     int64_t *h_out; // pinned host block that the width kernel writes its sums to (nullptr: none left)
     void *h_spec;   // pinned host memory for the spectra of short sides
-    void *io_mem;   // staging of lattice transfers, allocated by the first one
     int cus;        // the device's compute units
-    int device;     // device current at creation, whose static scratch okpz_psd_noalloc uses
+    int device;     // device current at creation, whose static scratch the handle uses
 };
 
 namespace {
@@ -201,7 +201,6 @@ void release(okpz_sim *s)
     if (!s) return;
     (void)hipStreamSynchronize(s->stream);
     if (s->psd_mem) (void)hipFree(s->psd_mem);
-    if (s->io_mem) (void)hipFree(s->io_mem);
     give_block(s->h_out);
     if (s->h_spec) (void)hipHostFree(s->h_spec);
     if (s->own_mem && s->mem) (void)hipFree(s->mem);
@@ -209,44 +208,33 @@ void release(okpz_sim *s)
     delete s;
 }
 
-// Spectrum scratch of okpz_psd_noalloc: one array per device, held until the
-// process ends, never allocated or freed by a call.  In host code `scratch`
-// names a host-side stand-in, not device memory: kernels and copies get the
-// device address that hipGetSymbolAddress returns for the current device.
-constexpr size_t kStaticPsdBytes = size_t(24) << 20;
+// In host code `scratch` names a host-side stand-in, not device memory: kernels and
+// copies get the device address that hipGetSymbolAddress returns for the current device.
 constexpr int64_t kStaticPsdMaxSide = int64_t(1) << 17;
-static __device__ __align__(256) unsigned char scratch[kStaticPsdBytes];
+static __device__ __align__(256) unsigned char scratch[okpz::StaticScratch::kBytes];
 
 constexpr size_t kPinnedSpectra = size_t(1) << 20;
 constexpr int kMaxDevices = 64;
-std::mutex g_static_mu;
-void *g_static_ptr[kMaxDevices];     // device address of `scratch` per device
-bool g_static_tried[kMaxDevices];
-hipError_t g_static_err[kMaxDevices];
+struct StaticArray {
+    std::mutex turn;
+    bool tried;
+    void *ptr;  // device address of `scratch` on this device
+    hipError_t err;
+};
+StaticArray g_static[kMaxDevices];
 
-// Once per device, with that device current (called from make_sim, the
-// library's set-up of every handle).
+// Once per device; `turn` is held.
 void static_scratch_setup(int dev)
 {
-    if (dev < 0 || dev >= kMaxDevices) return;
-    std::lock_guard<std::mutex> lock(g_static_mu);
-    if (g_static_tried[dev]) return;
-    g_static_tried[dev] = true;
-    void *ptr = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-    g_static_err[dev] = e;
-    g_static_ptr[dev] = e == hipSuccess ? ptr : nullptr;
-}
-
-void *static_scratch(int dev, hipError_t *err)
-{
-    if (dev < 0 || dev >= kMaxDevices) {
-        *err = hipErrorInvalidDevice;
-        return nullptr;
-    }
-    std::lock_guard<std::mutex> lock(g_static_mu);
-    *err = g_static_tried[dev] ? g_static_err[dev] : hipErrorNotInitialized;
-    return g_static_ptr[dev];
+    StaticArray &a = g_static[dev];
+    if (a.tried) return;
+    a.tried = true;
+    int now = dev;
+    a.err = hipGetDevice(&now);
+    if (a.err == hipSuccess && now != dev) a.err = hipSetDevice(dev);
+    if (a.err == hipSuccess) a.err = hipGetSymbolAddress(&a.ptr, HIP_SYMBOL(scratch));
+    if (a.err != hipSuccess) a.ptr = nullptr;
+    if (now != dev) (void)hipSetDevice(now);
 }
 
 int make_sim(okpz_sim **out, int64_t Lx, int64_t Ly, double p, double q, uint64_t seed,
@@ -286,7 +274,11 @@ int make_sim(okpz_sim **out, int64_t Lx, int64_t Ly, double p, double q, uint64_
         delete s;
         return hip_fail(ce, "hipDeviceGetAttribute");
     }
-    static_scratch_setup(s->device);
+    // (its address now, so that no later call is the first to load it)
+    if (s->device >= 0 && s->device < kMaxDevices) {
+        std::lock_guard<std::mutex> turn(g_static[s->device].turn);
+        static_scratch_setup(s->device);
+    }
     int rc = alloc_state(s, dev_buf, bytes, stream);
     if (rc != OKPZ_OK) {
         delete s;
@@ -311,17 +303,6 @@ int launch_flat(okpz_sim *s)
     return OKPZ_OK;
 }
 
-// The handle's staging buffer for lattice transfers (at most 16 MiB, kept until
-// okpz_free), or nullptr where no device memory is left.
-void *io_buffer(okpz_sim *s)
-{
-    if (!s->io_mem && hipMalloc(&s->io_mem, okpz::io_bytes(s->Lx, s->Ly)) != hipSuccess) {
-        (void)hipGetLastError();
-        s->io_mem = nullptr;
-    }
-    return s->io_mem;
-}
-
 okpz::LatticeView view_of(const okpz_sim *s, int copy, int32_t ox)
 {
     return okpz::LatticeView{s->buf[copy], (int32_t)s->Lx, (int32_t)s->Ly, s->W, ox};
@@ -336,8 +317,8 @@ bool planes_valid(const int64_t state[3], int64_t Lx, int64_t Ly)
 // physical column x of stored copy with offset ox: stored column (x - ox) mod Lx
 inline int64_t stored_col(int64_t x, int32_t ox, int64_t Lx) { return ((x - ox) % Lx + Lx) % Lx; }
 
-// Rows as canonical bytes without device memory of their own (the staging buffer
-// could not be allocated): packed rows to the host, unpacked there.
+// Rows as canonical bytes where the GPU's scratch cannot be had: packed rows to the
+// host, unpacked there.
 int get_rows_on_host(okpz_sim *s, int64_t y0, int64_t n, uint8_t *host)
 {
     const size_t W = (size_t)s->W;
@@ -357,7 +338,7 @@ int get_rows_on_host(okpz_sim *s, int64_t y0, int64_t n, uint8_t *host)
 }
 
 // A canonical lattice already known to be valid, packed on the host into copy 0
-// (one lattice copy, or no staging buffer).
+// (one lattice copy, or no scratch).
 int upload_lattice(okpz_sim *s, const uint8_t *host)
 {
     const size_t W = (size_t)s->W;
@@ -375,7 +356,7 @@ int upload_lattice(okpz_sim *s, const uint8_t *host)
     return OKPZ_OK;
 }
 
-// The same through the device: bytes in chunks of rows into the staging buffer,
+// The same through the device: bytes in chunks of rows into the staging memory io,
 // packed into the copy that the next sweep would overwrite and tested there, which
 // then becomes the current one.  *valid is 0, and the state as it was, for a lattice
 // that is no slope field.
@@ -405,6 +386,22 @@ int upload_lattice_checked(okpz_sim *s, const uint8_t *host, void *io, int *vali
 using okpz::host::CkptHeader;
 
 }  // namespace
+
+okpz::StaticScratch::StaticScratch(int device, hipStream_t stream)
+    : stream_(stream), mem_(nullptr), err_(hipErrorInvalidDevice)
+{
+    if (device < 0 || device >= kMaxDevices) return;
+    StaticArray &a = g_static[device];
+    turn_ = std::unique_lock<std::mutex>(a.turn);
+    static_scratch_setup(device);
+    mem_ = a.ptr;
+    err_ = a.err;
+}
+
+okpz::StaticScratch::~StaticScratch()
+{
+    if (mem_) (void)hipStreamSynchronize(stream_);
+}
 
 namespace okpz {
 
@@ -671,16 +668,16 @@ int okpz_psd_noalloc(okpz_sim *s, double *sx, double *sy)
                     "okpz_psd_noalloc: lattice %lldx%lld exceeds the static scratch's limit of "
                     "%lld sites per side",
                     (long long)s->Lx, (long long)s->Ly, (long long)kStaticPsdMaxSide);
-    const okpz::PsdPlan p = okpz::psd_plan_capped(s->Lx, s->Ly, kStaticPsdBytes);
-    if (p.bytes > kStaticPsdBytes)
+    const okpz::PsdPlan p = okpz::psd_plan_capped(s->Lx, s->Ly, okpz::StaticScratch::kBytes);
+    if (p.bytes > okpz::StaticScratch::kBytes)
         return fail(OKPZ_EINVAL, "okpz_psd_noalloc: %zu bytes of scratch needed, %zu available",
-                    p.bytes, kStaticPsdBytes);
-    hipError_t se;
-    void *mem = static_scratch(s->device, &se);
-    if (!mem) return hip_fail(se, "hipGetSymbolAddress(scratch)");
+                    p.bytes, okpz::StaticScratch::kBytes);
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    const okpz::StaticScratch turn(s->device, s->stream);
+    if (!turn.mem()) return hip_fail(turn.error(), "hipGetSymbolAddress(scratch)");
     okpz::LatticeView v{s->buf[s->cur], (int32_t)s->Lx, (int32_t)s->Ly, s->W, s->ox};
-    HIP_TRY(okpz::launch_psd(v, p, s->d_rows, mem, s->stream));
-    return copy_spectra(s, static_cast<const char *>(mem) + p.off_spec, sx, sy, false);
+    HIP_TRY(okpz::launch_psd(v, p, s->d_rows, turn.mem(), s->stream));
+    return copy_spectra(s, static_cast<const char *>(turn.mem()) + p.off_spec, sx, sy, false);
 }
 
 int okpz_time(const okpz_sim *s, int64_t *t)
@@ -706,11 +703,11 @@ int okpz_get_rows(okpz_sim *s, int64_t y0, int64_t nrows, uint8_t *host, size_t 
     if (nrows < 0 || nrows > s->Ly) return fail(OKPZ_EINVAL, "nrows out of range");
     if (bytes < (size_t)(nrows * s->Lx)) return fail(OKPZ_EINVAL, "host buffer too small");
     y0 = ((y0 % s->Ly) + s->Ly) % s->Ly;
-    void *io = io_buffer(s);
     HIP_TRY(hipStreamSynchronize(s->stream));
-    if (!io) return get_rows_on_host(s, y0, nrows, host);
-    HIP_TRY(okpz::download_rows(view_of(s, s->cur, s->ox), y0, nrows, host, io, okpz::io_bytes(s->Lx, s->Ly),
-                                s->stream));
+    const okpz::StaticScratch turn(s->device, s->stream);
+    if (!turn.mem()) return get_rows_on_host(s, y0, nrows, host);
+    HIP_TRY(okpz::download_rows(view_of(s, s->cur, s->ox), y0, nrows, host, turn.mem(),
+                                okpz::io_bytes(s->Lx, s->Ly), s->stream));
     return OKPZ_OK;
 }
 
@@ -727,11 +724,14 @@ int okpz_set_lattice(okpz_sim *s, const uint8_t *host, size_t bytes, int64_t H0,
     if (t < 0 || t >= (int64_t(1) << 32)) return fail(OKPZ_EINVAL, "t out of range");
     if (!okpz::host::valid_h0(H0))
         return fail(OKPZ_EINVAL, "height of site (0,0) must be even (h = x + y mod 2)");
-    void *io = s->copies == 2 ? io_buffer(s) : nullptr;
     int valid = 0;
-    if (io) {
-        const int rc = upload_lattice_checked(s, host, io, &valid);
-        if (rc != OKPZ_OK) return rc;
+    if (s->copies == 2) {
+        HIP_TRY(hipStreamSynchronize(s->stream));
+        const okpz::StaticScratch turn(s->device, s->stream);
+        if (turn.mem()) {
+            const int rc = upload_lattice_checked(s, host, turn.mem(), &valid);
+            if (rc != OKPZ_OK) return rc;  // (after the turn's copies from the caller's memory)
+        }
     }
     if (!valid) {  // not tested yet, or to say what is wrong
         std::string why;

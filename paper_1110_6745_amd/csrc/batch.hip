@@ -44,6 +44,7 @@
 #include "host_logic.h"
 #include "okpz.h"
 #include "state_io.h"
+#include "static_scratch.h"
 #include "sweep_core.h"
 #include "width.h"
 #include "width_core.h"
@@ -578,8 +579,7 @@ struct okpz_batch {
     std::vector<size_t> result_offs;
     std::unique_ptr<char[]> results;
     bool have_results = false;  // of the completed run (ran)
-    void *io_mem = nullptr;  // staging of okpz_batch_get_lattice, allocated by the first one
-    size_t io_size = 0;
+    int device = 0;  // current at creation, whose static scratch stages lattices
     JobDesc *d_desc = nullptr;
     JobState *d_state = nullptr;
     Control *d_ctl = nullptr;
@@ -909,9 +909,8 @@ int okpz_batch_create(okpz_batch **out, const okpz_job *jobs, int32_t n_jobs, do
             }
         }
     }
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, dev);
+    (void)hipGetDevice(&b->device);
+    (void)hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, b->device);
     if (b->cus <= 0) b->cus = 256;
     // an all-(1, 0) table runs the growth-only kernel, whose step loops stay
     // free of spills at 1024 threads and two workgroups per CU
@@ -1235,21 +1234,14 @@ int okpz_batch_get_lattice(okpz_batch *b, int32_t job, uint8_t *host, size_t byt
     JobState st;
     BHIP(hipMemcpy(&st, b->d_state + job, sizeof st, hipMemcpyDeviceToHost));
     const okpz::LatticeView v{d.buf[st.cur], d.Lx, d.Ly, d.W, st.ox};
-    if (!b->io_mem) {  // for the largest job of the batch, at most 16 MiB
-        size_t size = 0;
-        for (const JobDesc &o : b->desc) size = std::max(size, okpz::io_bytes(o.Lx, o.Ly));
-        if (hipMalloc(&b->io_mem, size) == hipSuccess) {
-            b->io_size = size;
-        } else {
-            (void)hipGetLastError();
-            b->io_mem = nullptr;
+    {
+        const okpz::StaticScratch turn(b->device, b->stream);
+        if (turn.mem()) {
+            BHIP(okpz::download_rows(v, 0, d.Ly, host, turn.mem(), okpz::io_bytes(d.Lx, d.Ly), b->stream));
+            return OKPZ_OK;
         }
     }
-    if (b->io_mem) {
-        BHIP(okpz::download_rows(v, 0, d.Ly, host, b->io_mem, b->io_size, b->stream));
-        return OKPZ_OK;
-    }
-    // no device memory left for the staging: unpacked on the host
+    // the GPU's scratch cannot be had: unpacked on the host
     std::vector<uint32_t> pl(2 * (size_t)d.Ly * d.W);
     BHIP(hipMemcpy(pl.data(), d.buf[st.cur], pl.size() * 4, hipMemcpyDeviceToHost));
     for (int64_t y = 0; y < d.Ly; ++y)
@@ -1267,7 +1259,6 @@ int okpz_batch_free(okpz_batch *b)
     if (!b) return OKPZ_OK;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     if (b->mem) (void)hipFree(b->mem);
-    if (b->io_mem) (void)hipFree(b->io_mem);
     if (b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
     return OKPZ_OK;

@@ -22,9 +22,14 @@ Lx, Ly = 320, 256
 make = okpz.okpz_init if {copies} == 2 else okpz.okpz_init_in_place
 other = make(Lx, Ly, 1.0, 0.0, 2)
 other.sweep(2)
-other.width(), other.w2(), other.psd_noalloc()  # the runtime's own first-use work is done by another handle
+# the runtime's own first-use work is done by another handle
+lat = other.get_lattice()
+other.set_lattice(lat, 0, 0)
+other.width(), other.w2(), other.psd_noalloc()
 sim = make(Lx, Ly, 1.0, 0.0, 1)
 sim.sweep(3)
+batch = okpz.Batch([(64, 32, 1.0, 0.0, 1, 5)], 0.5)
+batch.run()
 os.write(2, b"\\nMARK begin\\n")
 {call}
 os.write(2, b"\\nMARK end\\n")
@@ -36,6 +41,10 @@ CALLS = {
     "psd_noalloc": "sim.psd_noalloc()",
     "width": "sim.width()",
     "w2": "sim.w2()",
+    "get_lattice": "sim.get_lattice()",
+    "get_rows": "sim.get_rows(3, 5)",
+    "set_lattice": "sim.set_lattice(lat, 0, 0)",
+    "batch_get_lattice": "batch.get_lattice(0)",
 }
 
 
@@ -78,4 +87,41 @@ def test_measurements_of_many_handles():
     for seed, sim in sims.items():
         assert sim.width() == want(seed), seed
     for sim in sims.values():
+        sim.free()
+
+
+def test_transfers_and_spectra_of_several_threads():
+    # all of them use the GPU's one scratch, in turns
+    import threading
+
+    import numpy as np
+
+    from paper_1110_6745_amd import okpz
+    from tests import inputs
+
+    sizes = [(4096, 4096), (320, 4096), (8192, 2080), (96, 64)]
+    lats = [inputs.separable_rows(inputs.balanced_bits(Lx, i), inputs.balanced_bits(Ly, i + 9), 0, Ly)
+            for i, (Lx, Ly) in enumerate(sizes)]
+    sims = [okpz.okpz_init(Lx, Ly, 1.0, 0.0, 1) for Lx, Ly in sizes]
+    spectra, wrong = [], []
+    for sim, lat in zip(sims, lats):
+        sim.set_lattice(lat, 0, 0)
+        spectra.append(sim.psd())
+
+    def work(i):
+        for _ in range(4):
+            sims[i].set_lattice(lats[i], 2 * i, 1)
+            if not np.array_equal(sims[i].get_lattice(), lats[i]):
+                wrong.append((sizes[i], "lattice"))
+            if not all(np.array_equal(a, b) for a, b in zip(sims[i].psd_noalloc(), spectra[i])):
+                wrong.append((sizes[i], "spectrum"))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(sizes))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(100)
+    assert not any(t.is_alive() for t in threads)
+    assert not wrong, wrong
+    for sim in sims:
         sim.free()
