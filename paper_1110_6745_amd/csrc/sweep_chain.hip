@@ -8,6 +8,12 @@
 // sweep's 64 barriered steps; a launch of its own per sweep adds about a
 // microsecond to it (256 x 256, p = 1, q = 0: 17.9 us per sweep in launches of
 // one, 16.9 us in launches of ten).
+//
+// Unlike the other 1024-thread kernels these may take more than 80 scalar registers, which
+// leaves them one workgroup per CU: a launch is one workgroup, and the four hardware queues
+// of a process run four such launches at a time (64 to 512 lattices of 256 x 256 on
+// streams of their own: 4.26 us per sweep and lattice, a quarter of one lattice's
+// 16.9).  Capped at 80 they spill scalar registers and a sweep is 1 to 4 % slower.
 #include "sweep_core.h"
 
 namespace okpz {
