@@ -55,7 +55,6 @@ namespace batch {
 struct JobDesc {
     uint32_t *buf[2];
     int64_t *h0;
-    int64_t *rows;      // width scratch of the per-lattice width launches (served large jobs)
     int64_t *samples;   // nsamp x 6: t, S1' lo, S1' hi, S2' lo, S2' hi, H0
     const int32_t *sample_t;
     int32_t nsamp;
@@ -831,7 +830,6 @@ int okpz_batch_create(okpz_batch **out, const okpz_job *jobs, int32_t n_jobs, do
     b->desc.resize(n_jobs);
     // layout: descriptors, states, control, ring, then per-job lattices etc.
     size_t total = al(n_jobs * sizeof(JobDesc)) + al(n_jobs * sizeof(JobState)) + al(sizeof(Control));
-    uint64_t groups = 0;
     std::vector<size_t> offs(n_jobs);
     b->result_offs.resize(n_jobs);
     for (int r = 0; r < n_jobs; ++r) {
@@ -863,14 +861,12 @@ int okpz_batch_create(okpz_batch **out, const okpz_job *jobs, int32_t n_jobs, do
         d.t_max = (int32_t)j.t_max;
         b->times[r] = sample_times(j.t_max, m);
         d.nsamp = (int32_t)b->times[r].size();
-        groups += d.ngroups;
         offs[r] = total;
         const size_t lat = al(2 * (size_t)j.Ly * (size_t)(j.Lx / 32) * 4);
-        total += 2 * lat + al(3 * (size_t)j.Ly * 8) + al(4 * (size_t)std::max(1, d.nsamp));
+        total += 2 * lat + al(4 * (size_t)std::max(1, d.nsamp));
         b->result_offs[r] = b->results_size;
         b->results_size += al(8) + al(6 * 8 * (size_t)std::max(1, d.nsamp));
     }
-    (void)groups;
     const size_t roff = total;
     total += b->results_size;
     const size_t qoff = total;
@@ -895,10 +891,9 @@ int okpz_batch_create(okpz_batch **out, const okpz_job *jobs, int32_t n_jobs, do
         const size_t lat = al(2 * (size_t)j.Ly * (size_t)(j.Lx / 32) * 4);
         d.buf[0] = reinterpret_cast<uint32_t *>(p);
         d.buf[1] = reinterpret_cast<uint32_t *>(p + lat);
-        d.rows = reinterpret_cast<int64_t *>(p + 2 * lat);
         d.h0 = reinterpret_cast<int64_t *>(b->d_results + b->result_offs[r]);
         d.samples = d.h0 + al(8) / 8;
-        int32_t *tt = reinterpret_cast<int32_t *>(p + 2 * lat + al(3 * (size_t)j.Ly * 8));
+        int32_t *tt = reinterpret_cast<int32_t *>(p + 2 * lat);
         d.sample_t = tt;
         if (d.nsamp) {
             e = hipMemcpy(tt, b->times[r].data(), d.nsamp * 4, hipMemcpyHostToDevice);
@@ -1303,6 +1298,7 @@ struct ServeJob {
     size_t bytes = 0;
     void *mem = nullptr;
     JobDesc desc{};
+    int64_t *rows = nullptr;  // width scratch of the per-lattice launches (large jobs)
     std::vector<int32_t> times;
     int32_t s = 0;  // MCS completed (host mirror)
     // large lattices run as plain per-lattice sweeps (see okpz_serve_step);
@@ -1455,7 +1451,7 @@ int admit(okpz_server *sv, ServeJob &J, int slot, double t)
     d.buf[0] = reinterpret_cast<uint32_t *>(p);
     d.buf[1] = reinterpret_cast<uint32_t *>(p + lat);
     d.h0 = reinterpret_cast<int64_t *>(p + 2 * lat);
-    d.rows = reinterpret_cast<int64_t *>(p + 2 * lat + al(8));
+    J.rows = reinterpret_cast<int64_t *>(p + 2 * lat + al(8));
     const size_t rows_b = al((okpz::width_scratch_words(j.Ly) + 4) * 8);
     d.samples = reinterpret_cast<int64_t *>(p + 2 * lat + al(8) + rows_b);
     int32_t *tt = reinterpret_cast<int32_t *>(p + 2 * lat + al(8) + rows_b +
@@ -1525,7 +1521,7 @@ int grid_sweep(okpz_server *sv, ServeJob &J, hipStream_t stream)
     if (J.next_sample < d.nsamp && J.times[J.next_sample] == J.s) {
         const okpz::LatticeView v{d.buf[J.cur], d.Lx, d.Ly, d.W, J.ox};
         // a sample is t, then what the width launch writes
-        e = okpz::launch_width(v, d.rows, d.h0, d.samples + 6 * (size_t)J.next_sample + 1, J.s,
+        e = okpz::launch_width(v, J.rows, d.h0, d.samples + 6 * (size_t)J.next_sample + 1, J.s,
                                stream);
         if (e != hipSuccess) return bfail(OKPZ_EDEVICE, "serve width: %s", hipGetErrorString(e));
         ++J.next_sample;

@@ -280,8 +280,8 @@ int rows_per_wave(int64_t Ly) { return (int)((Ly + kWaves * 2048 - 1) / (kWaves 
 
 }  // namespace
 
-// the batch kernel's and the spectrum's rows; the records (at most one per kWaves
-// rows) use their place
+// The spectrum's rows (psd.h: 3 Ly words at most); the width's records (four words per
+// kWaves rows at most) use their place.
 size_t width_scratch_words(int64_t Ly) { return 3 * (size_t)Ly + 4 * (size_t)((Ly + 255) / 256) + 4; }
 
 hipError_t launch_width(const LatticeView &v, int64_t *rows, const int64_t *h0, int64_t *out, int64_t t,

@@ -125,3 +125,20 @@ def test_transfers_and_spectra_of_several_threads():
     assert not wrong, wrong
     for sim in sims:
         sim.free()
+
+
+def test_batch_memory():
+    # two copies of each lattice (16 bytes per row of 32 sites), and little else
+    import torch
+
+    from paper_1110_6745_amd import okpz
+
+    n, Ly = 2000, 8192
+    torch.cuda.init()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    batch = okpz.Batch([(32, Ly, 1.0, 0.0, i, 1) for i in range(n)], 0.5)
+    used = free - torch.cuda.mem_get_info()[0]
+    copies = n * 16 * Ly
+    assert used <= copies + n * 1024 + (4 << 20), (used, copies)
+    batch.free()
