@@ -202,7 +202,10 @@ __device__ __forceinline__ int items_per_claim(int32_t nitems, int32_t flags)
 // 21.0 / 17.8 / 18.1 / 26.0, 64 (2) 20.6 / 23.6 / 18.6 / 26.5, 96 (3) 27.3 / 22.6 / 24.8 / 20.9,
 // 256 of 32^2 to 1024^2 (3) 101.8 / 98.5 / 101.3 / 102.6, 384 (4.5) 102.1 / 102.7 / 97.4 / 91.9,
 // 512 (6) 191.5 / 192.3 / 177.3 / 167.0; 128 up to 896^2 at p = 0.95, q = 0.05, 512 threads
-// (1.1) 41.5 / 29.7 / 56.4 / 61.2.
+// (1.1) 41.5 / 29.7 / 56.4 / 61.2.  The line at 3.5 lies between what was measured at 3, where
+// the best policy depends on the mix (teams by 4 % for the jobs of 32^2 to 1024^2, sticky
+// pairs by 8 % for the equal ones of 1024^2, which this line costs them), and at 4.5, where sticky
+// pairs win.  At 512 threads there is the one point: the lines are those of 1024.
 inline int32_t claim_policy(int64_t items, int64_t workgroups)
 {
     if (2 * items <= 3 * workgroups) return kClaimStay + kClaimItems;
